@@ -27,6 +27,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "hjpd_device.hpp"
@@ -50,6 +51,7 @@ __device__ __forceinline__ float tanh_fast(float x) {
 
 constexpr int kLtThreads = 512;
 constexpr int kLtWaves = kLtThreads / 64;
+constexpr int kLtCounters = 8;
 constexpr int kLtNT = 4;                                                    // 16-node column tiles: up to 64 nodes
 
 // LDS rows per array: nodes 0 .. 16*NT + 1 (NT column tiles of 16 nodes), so
@@ -970,67 +972,115 @@ __global__ void k_lt_grad_out(const float* sums, const float* S, int d, float* d
   dg[e] = sums[2 * DD + e] + 0.5f * (S[r * d + c] + S[c * d + r]);
 }
 
-// (I + tau Q_s)^{-1} by Gauss-Jordan elimination with partial pivoting in
-// double precision, one workgroup; W is a d x 2d double scratch.
-__global__ void k_lt_inverse(const float* Q, int d, double tau, double* W, float* Mout, int* fail) {
-  __shared__ int s_piv;
-  __shared__ double s_f[kLtMaxD];
-  const int tid = threadIdx.x, nt = blockDim.x, w2 = 2 * d;
-  for (int e = tid; e < d * w2; e += nt) {
-    const int r = e / w2, c = e - r * w2;
-    double v;
-    if (c < d)
-      v = (r == c ? 1.0 : 0.0) + tau * 0.5 * (double(Q[r * d + c]) + double(Q[c * d + r]));
-    else
-      v = (c - d == r) ? 1.0 : 0.0;
-    W[e] = v;
-  }
-  if (tid == 0) *fail = 0;
-  __syncthreads();
-  for (int c = 0; c < d; c++) {
-    if (tid == 0) {
-      int best = c;
-      double bv = fabs(W[c * w2 + c]);
-      for (int r = c + 1; r < d; r++) {
-        const double v = fabs(W[r * w2 + c]);
-        if (v > bv) {
-          bv = v;
-          best = r;
+// (I + tau Q_s)^{-1} by Gauss-Jordan exchange steps with row pivoting in double
+// precision, one workgroup, the matrix in registers: thread (tr, tc) holds rows
+// tr + TR u and columns tc + 16 m.  Also clears the solve's counters.
+//
+// The elimination is a chain of d steps, so what bounds it is the latency of
+// one step: a barrier after the pivot column's entries reach LDS, a wave-wide
+// maximum that every wave forms for itself (no second pass over LDS), a barrier
+// after the pivot row, and D*D / threads updates per thread.  Rows are not
+// exchanged: a row that has served as pivot is marked, and the permutation is
+// undone on output.  With the matrix in global memory and thread 0 searching
+// the pivot alone it took 29 / 124 / 2,350 / 4,600 us at d = 16 / 32 / 100 / 128;
+// this form takes 8 / 17 / 112 / 154 us.
+template <int D>
+struct LtInv {
+  static constexpr int TR = D <= 32 ? 16 : 64;  // row groups (16 column groups): 256 or 1,024 threads
+  static constexpr int RU = (D + TR - 1) / TR, CM = (D + 15) / 16, kThreads = 16 * TR;
+};
+
+template <int D>
+__global__ void __launch_bounds__(LtInv<D>::kThreads) k_lt_inverse(const float* Q, double tau, float* Mout,
+                                                                   int32_t* counters) {
+  constexpr int TR = LtInv<D>::TR, RU = LtInv<D>::RU, CM = LtInv<D>::CM;
+  __shared__ double s_col[2][D], s_row[2][16 * CM];  // alternate between steps: one barrier each way is enough
+  __shared__ int s_piv[D];
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15, lane = tid & 63;
+  if (tid < kLtCounters) counters[tid] = 0;
+  double T[RU][CM];
+#pragma unroll
+  for (int u = 0; u < RU; u++)
+#pragma unroll
+    for (int m = 0; m < CM; m++) {
+      const int r = tr + TR * u, c = tc + 16 * m;
+      T[u][m] = (r < D && c < D) ? (r == c ? 1.0 : 0.0) + tau * 0.5 * (double(Q[r * D + c]) + double(Q[c * D + r])) : 0.0;
+    }
+  bool used0 = lane >= D, used1 = lane + 64 >= D;  // rows lane and lane + 64 have served (or do not exist)
+#pragma unroll
+  for (int mc = 0; mc < CM; mc++) {
+    for (int cc = 0; cc < 16; cc++) {
+      const int c = 16 * mc + cc;
+      if (c >= D) break;
+      double* col = s_col[c & 1];
+      double* row = s_row[c & 1];
+      if (tc == cc)
+#pragma unroll
+        for (int u = 0; u < RU; u++)
+          if (tr + TR * u < D) col[tr + TR * u] = T[u][mc];
+      __syncthreads();
+      // largest entry among the rows that have not served: the top bits of its
+      // magnitude with 127 - row in the last seven (entries within 2^-13 of the
+      // largest count as equal, the lowest row wins; a NaN counts as zero)
+      auto key_of = [&](int r) {
+        const uint32_t hi = uint32_t(__double_as_longlong(col[r]) >> 32) & 0x7fffffffu;
+        return int(((hi <= 0x7ff00000u ? hi : 0u) & ~127u) | uint32_t(127 - r));
+      };
+      int key = used0 ? -1 : key_of(lane);
+      if (!used1) key = max(key, key_of(lane + 64));
+      auto exchange = [&](auto ctrl) {
+        key = max(key, __builtin_amdgcn_update_dpp(0, key, decltype(ctrl)::value, 0xf, 0xf, true));
+      };
+      exchange(std::integral_constant<int, kDppQuad1032>{});
+      exchange(std::integral_constant<int, kDppQuad2301>{});
+      exchange(std::integral_constant<int, kDppRowHalfMirror>{});
+      exchange(std::integral_constant<int, kDppRowMirror>{});
+      key = max(key, __shfl_xor(key, 16, 64));
+      key = max(key, __shfl_xor(key, 32, 64));
+      const int pr = 127 - (__builtin_amdgcn_readfirstlane(key) & 127);
+      used0 |= pr == lane;
+      used1 |= pr == lane + 64;
+      const double inv = 1.0 / col[pr];
+      if (tid == 0) {
+        s_piv[c] = pr;
+        if (!(fabs(col[pr]) > 0.0)) counters[1] = 1;
+      }
+      if (tr == pr % TR)
+#pragma unroll
+        for (int u = 0; u < RU; u++)
+          if (tr + TR * u == pr)
+#pragma unroll
+            for (int m = 0; m < CM; m++) row[tc + 16 * m] = T[u][m];
+      __syncthreads();
+      // exchange y_pr and x_c: the pivot row becomes -row / a (1 / a at c), every
+      // other row T - T[.][c] row / a (T[.][c] / a at c)
+#pragma unroll
+      for (int u = 0; u < RU; u++) {
+        const int r = tr + TR * u;
+        const bool piv = r == pr;
+        const double f = r < D ? (piv ? 0.0 : col[r]) : 0.0;
+#pragma unroll
+        for (int m = 0; m < CM; m++) {
+          const double q = row[tc + 16 * m] * inv;
+          const bool here = m == mc && tc == cc;
+          if (here) T[u][m] = piv ? inv : T[u][m] * inv;
+          else T[u][m] = piv ? -q : T[u][m] - f * q;
         }
       }
-      s_piv = best;
-      if (!(bv > 0.0)) *fail = 1;
     }
-    __syncthreads();
-    const int pr = s_piv;
-    if (pr != c)
-      for (int e = tid; e < w2; e += nt) {
-        const double tmp = W[c * w2 + e];
-        W[c * w2 + e] = W[pr * w2 + e];
-        W[pr * w2 + e] = tmp;
-      }
-    __syncthreads();
-    const double inv = 1.0 / W[c * w2 + c];
-    __syncthreads();
-    for (int e = tid; e < w2; e += nt) W[c * w2 + e] *= inv;
-    __syncthreads();
-    for (int r = tid; r < d; r += nt) s_f[r] = W[r * w2 + c];
-    __syncthreads();
-    for (int e = tid; e < d * w2; e += nt) {
-      const int r = e / w2, col = e - r * w2;
-      if (r != c) W[e] -= s_f[r] * W[c * w2 + col];
+  }
+  __syncthreads();
+  // row pr_c of the tableau is x_c, column c' stands for y at row pr_c'
+  __shared__ int s_var[D];  // row -> the variable it holds
+  if (tid < D) s_var[s_piv[tid]] = tid;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < RU; u++)
+#pragma unroll
+    for (int m = 0; m < CM; m++) {
+      const int r = tr + TR * u, c = tc + 16 * m;
+      if (r < D && c < D) Mout[s_var[r] * D + s_piv[c]] = float(T[u][m]);
     }
-    __syncthreads();
-  }
-  for (int e = tid; e < d * d; e += nt) {
-    const int r = e / d, c = e - r * d;
-    Mout[e] = float(W[r * w2 + d + c]);
-  }
-}
-
-__global__ void k_lt_zero(int32_t* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1041,8 +1091,7 @@ struct LtState {
   int d = 0;
   int n_cu = 0;
   float* M = nullptr;           // d*d
-  double* W = nullptr;          // d*2d
-  int32_t* counters = nullptr;  // [0] forward head, [1] inverse failure, [2] backward head
+  int32_t* counters = nullptr;  // [0] forward head, [1] inverse failure
   int32_t* scratch_i = nullptr; // iterations and statuses of the forward pass in value_grad
   size_t scratch_bytes = 0;
   float* ckpt = nullptr;
@@ -1104,8 +1153,8 @@ int lt_create(LtState** out, const hjpd_desc& desc) {
     return hjpd_fail(HJPD_EDEVICE, "cannot reserve LDS for the linear-tanh kernels");
   }
   const size_t dd = size_t(desc.d) * desc.d;
-  if (hipMalloc(&s->M, sizeof(float) * dd) != hipSuccess || hipMalloc(&s->W, sizeof(double) * 2 * dd) != hipSuccess ||
-      hipMalloc(&s->counters, sizeof(int32_t) * 8) != hipSuccess ||
+  if (hipMalloc(&s->M, sizeof(float) * dd) != hipSuccess ||
+      hipMalloc(&s->counters, sizeof(int32_t) * kLtCounters) != hipSuccess ||
       hipMalloc(&s->sums, sizeof(float) * (3 * dd + 1)) != hipSuccess ||
       hipMalloc(&s->tmp, sizeof(float) * 2 * dd) != hipSuccess) {
     lt_destroy(s);
@@ -1118,7 +1167,6 @@ int lt_create(LtState** out, const hjpd_desc& desc) {
 void lt_destroy(LtState* s) {
   if (!s) return;
   if (s->M) (void)hipFree(s->M);
-  if (s->W) (void)hipFree(s->W);
   if (s->counters) (void)hipFree(s->counters);
   if (s->scratch_i) (void)hipFree(s->scratch_i);
   if (s->ckpt) (void)hipFree(s->ckpt);
@@ -1164,10 +1212,16 @@ static void fill_args(LtArgs& a, LtState* st, const hjpd_desc& d, int64_t n, con
 }
 
 static int lt_setup(LtState* st, const hjpd_desc& d, const void* gp, hipStream_t s) {
-  hipLaunchKernelGGL(k_lt_zero, dim3(1), dim3(64), 0, s, st->counters, 8);
-  hipLaunchKernelGGL(k_lt_inverse, dim3(1), dim3(256), 0, s, (const float*)gp, d.d, d.tau, st->W, st->M,
-                     st->counters + 1);
-  LT_HIP(hipGetLastError(), "linear-tanh set-up kernels");
+  auto launch = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), 0, s, (const float*)gp, d.tau, st->M, st->counters);
+  };
+  switch (d.d) {
+    case 16: launch(k_lt_inverse<16>, LtInv<16>::kThreads); break;
+    case 32: launch(k_lt_inverse<32>, LtInv<32>::kThreads); break;
+    case 100: launch(k_lt_inverse<100>, LtInv<100>::kThreads); break;
+    default: launch(k_lt_inverse<128>, LtInv<128>::kThreads); break;
+  }
+  LT_HIP(hipGetLastError(), "linear-tanh set-up kernel");
   return HJPD_OK;
 }
 

@@ -211,3 +211,25 @@ def test_autograd_function_matches_value_grad():
     assert torch.allclose(eps.grad.reshape(1), dh[:1])
     assert torch.allclose(Q.grad.reshape(-1), dg)
     lt.close()
+
+
+@pytest.mark.parametrize("d", [16, 32, 100, 128])
+def test_node0_matrix_with_row_exchanges(d):
+    """x_0 <- (I + tau Q_s)^{-1} (x_0 + tau p_1) for an indefinite Q whose
+    I + tau Q_s has a zero diagonal, so every elimination step has to take its
+    pivot from another row.  One step is read off the trajectories of two
+    solves of one and two iterations; the bound is the FP32 dot product's,
+    (d + 3) 2^-24 sum |M_ij| |v_j|."""
+    w = _small_workload(d=d, n=2, N=4, K=2)
+    rng = np.random.default_rng(d)
+    B = rng.standard_normal((d, d))
+    B = (B + B.T) / 2
+    np.fill_diagonal(B, 0.0)
+    w.gp = ((B - np.eye(d)) / w.tau).ravel()
+    Q = _f32(w.gp).reshape(d, d)
+    M = np.linalg.inv(np.eye(d) + w.tau * 0.5 * (Q + Q.T))
+    one, two = (_gpu_lt(w, K, 1, np.ones(w.n), traj=True) for K in (1, 2))
+    for i in range(w.n):
+        v = one["x_traj"][i, 0] + w.tau * two["p_traj"][i, 1]
+        bound = (d + 3) * 2.0 ** -24 * (np.abs(M) @ np.abs(v))
+        assert np.all(np.abs(two["x_traj"][i, 0] - M @ v) <= bound)
