@@ -7,14 +7,10 @@
 //   primal x_j <- x_j - tau (p_j - p_{j+1}) - tau delta (A^T p_j + eps (1 - tanh^2 x_j) p_j)
 //   extrapolation z = x_new + theta (x_new - x_old).
 //
-// Forward kernel: one point per workgroup of eight wave64s, the stacked state
-// X, P, Z [(N+1) x d] in LDS (row stride d+1).  The dense products A X and
-// A^T P over all nodes of the point are matrix-core GEMMs
-// (v_mfma_f32_16x16x4_f32): wave w owns output row tile w (rows 16w .. 16w+15)
-// and keeps those rows of A and A^T as MFMA A-operand fragments in registers
-// for the whole kernel; B operands are read from LDS.  Elementwise steps run on
-// the VALU in the accumulator layout; the node-0 product with M runs on the
-// VALU.  Workgroups are persistent and pop points from a counter.
+// Forward kernel (k_lt_forward): the iteration of hjpd_lt_core.hpp on a state
+// that stays in registers, one point per wave (d = 16, 32) or per workgroup of
+// eight waves (d = 100, 128).  Workgroups are persistent and pop points from a
+// counter; the kernel is compiled for one to four 16-node column tiles.
 //
 // Reverse mode (hjpd_value_grad): the forward pass stores the state every E
 // iterations; the backward kernel, per point, recomputes each segment of E
@@ -24,30 +20,16 @@
 // VJP's dense products A xbar and A^T vbar reuse the forward fragments; the
 // parameter gradient dA = sum of outer products over nodes is an MFMA product
 // accumulated in registers; dM and the direct dQ term are rank-1 VALU updates.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
 #include <type_traits>
 #include <vector>
 
-#include "hjpd_device.hpp"
-#include "hjpd_lintanh.hpp"
+#include "hjpd_lt_core.hpp"
 
 namespace hjpd {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// tanh from the exponential, tanh|x| = 1 - 2 / (exp(2|x|) + 1), sign restored:
-// one hardware exp and one reciprocal; absolute error at FP32 rounding level.
-__device__ __forceinline__ float tanh_fast(float x) {
-  const float e = __expf(2.f * fabsf(x));
-  const float t = 1.f - 2.f * __builtin_amdgcn_rcpf(e + 1.f);
-  return copysignf(t, x);
-}
 
 constexpr int kLtThreads = 512;
 constexpr int kLtWaves = kLtThreads / 64;
@@ -57,7 +39,6 @@ constexpr int kLtNT = 4;                                                    // 1
 // LDS rows per array: nodes 0 .. 16*NT + 1 (NT column tiles of 16 nodes), so
 // every GEMM column read and every j+1 read stays inside the array.
 __host__ __device__ constexpr int lt_rows(int N_max) { return 16 * ((N_max + 15) / 16) + 2; }
-inline size_t lt_lds_forward(int d, int N_max) { return size_t(3) * lt_rows(N_max) * (d + 1) * sizeof(float); }
 inline size_t lt_lds_backward(int d, int N_max) { return size_t(5) * lt_rows(N_max) * (d + 1) * sizeof(float); }
 // Per-workgroup reverse-mode buffer (floats): E recomputed steps of (x^k, p^{k+1}) in the LDS layout,
 // the saved adjoint (3 arrays), and E staged (XB_0, w) pairs for dM.
@@ -65,30 +46,6 @@ __host__ __device__ inline int64_t lt_seg_floats(int d, int N_max, int E) {
   const int64_t CK = int64_t(N_max + 1) * d, RL = int64_t(lt_rows(N_max)) * (d + 1);
   return int64_t(E) * 2 * RL + 3 * CK + int64_t(E) * 2 * d;
 }
-
-struct LtArgs {
-  const float* x;
-  const float* t;
-  const int32_t* N;
-  const float* hp;  // [eps, A (d*d)]
-  const float* Q;   // [d*d]
-  const float* M;   // (I + tau Q_s)^{-1}
-  float* phi;
-  float* xtraj;
-  float* ptraj;
-  int32_t* iters;
-  int32_t* status;
-  int32_t* head;
-  int64_t n;
-  float sigma, tau, theta, tol;
-  int max_iter, fixed, N_max;
-  uint64_t seed;
-  // checkpoints: per point n_ckpt + 1 snapshots of (X, P, Z), each 3 (N_max+1) d;
-  // snapshot c holds the state before iteration c E, the last one the final state
-  float* ckpt;
-  int ckpt_every;
-  int n_ckpt;
-};
 
 struct LtBwdArgs {
   LtArgs f;
@@ -462,112 +419,148 @@ __device__ void lt_load_fragments(const float* A, int wave, int lr, int lk, floa
   }
 }
 
+// t > 0, 1 <= N <= N_max, x finite; the whole wave calls it for one point.
 template <int D>
-__global__ void __launch_bounds__(kLtThreads, 4) k_lt_forward(LtArgs a) {
-  static_assert(D % 4 == 0, "d must be a multiple of 4");
-  constexpr int LD = D + 1;
-  extern __shared__ float smem[];
-  __shared__ float s_red[2 * kLtWaves];
-  __shared__ int s_pt;
-  const LtLane<D> L;
-  const int R = lt_rows(a.N_max);
-  const int NT = (a.N_max + 15) / 16;
-  float* sX = smem;
-  float* sP = sX + R * LD;
-  float* sZ = sP + R * LD;
-  const float eps = a.hp[0];
-  float af[D / 4], atf[D / 4];
-  lt_load_fragments<D>(a.hp + 1, L.wave, L.lr, L.lk, af, atf);
+__device__ __forceinline__ bool lt_bad_point(const LtArgs& a, int64_t pt) {
+  const int lane = threadIdx.x & 63;
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < (D + 63) / 64; i++) bad = bad || (lane + 64 * i < D && !__builtin_isfinite(a.x[pt * D + lane + 64 * i]));
+  const float t = a.t[pt];
+  const int N = a.N[pt];
+  return __any(bad || !(t > 0.f) || !__builtin_isfinite(t) || N < 1 || N > a.N_max);
+}
 
+template <int D, int NT, int KIND>
+__device__ __forceinline__ void lt_forward_wave(const LtArgs& a, float* smem, int* s_pt) {
+  using S = LtShape<D, NT>;
+  LtCore<D, NT, KIND> c;
+  c.setup(a, smem);
+  const float eps = a.hp[0];
+  const int64_t slot = 3 * int64_t(a.N_max + 1) * D;
   for (;;) {
-    if (L.tid == 0) s_pt = atomicAdd(a.head, 1);
-    __syncthreads();
-    const int64_t pt = s_pt;
-    __syncthreads();
+    int pop = 0;
+    if (c.tid == 0) pop = atomicAdd(a.head, 1);
+    if constexpr (S::W > 1) {
+      if (c.tid == 0) *s_pt = pop;
+      __syncthreads();
+      pop = *s_pt;
+      __syncthreads();
+    }
+    const int64_t pt = __builtin_amdgcn_readfirstlane(pop);
     if (pt >= a.n) break;
-    if (lt_bad_input<D>(a, pt)) {
-      if (L.tid == 0) {
+    if (lt_bad_point<D>(a, pt)) {
+      if (c.tid == 0) {
         if (a.phi) a.phi[pt] = NAN;
         a.iters[pt] = 0;
         a.status[pt] = kBadInput;
       }
       continue;
     }
-    const int Np = a.N[pt];
-    const float delta = a.t[pt] / float(Np);
-    lt_init<D>(a, pt, Np, R, sX, sP, sZ);
-    const int64_t slot = 3 * int64_t(a.N_max + 1) * D;
-    int k = 0, st = kMaxIter;
-    for (;;) {
-      if (a.ckpt && k % a.ckpt_every == 0 && k / a.ckpt_every < a.n_ckpt)
-        lt_save<D>(sX, sP, sZ, Np, a.N_max, a.ckpt + (pt * (a.n_ckpt + 1) + k / a.ckpt_every) * slot);
-      const bool need_res = !a.fixed || k + 1 >= a.max_iter;
-      float rx = 0.f, rp = 0.f;
-      lt_iterate<D>(L, a, af, atf, sX, sP, sZ, Np, NT, delta, eps, nullptr, nullptr, rx, rp);
-      k++;
-      bool done = k >= a.max_iter;
-      if (need_res) {
-        const float rxs = wg_sum(rx, s_red);
-        const float rps = wg_sum(rp, s_red + kLtWaves);
-        const bool fin = __builtin_isfinite(rxs + rps);
-        const bool small = rxs < a.tol && rps < a.tol;
-        if (!fin) {
-          st = kNonFinite;
-          done = true;
-        } else if (small && (!a.fixed || done)) {
-          st = kConverged;
-          done = true;
-        }
+    c.set_point(a, pt);
+    c.start(a, pt);
+    float* snap = a.ckpt ? a.ckpt + pt * (a.n_ckpt + 1) * slot : nullptr;
+    int k = 0, st = kMaxIter, next_snap = 0, snaps = 0;
+    auto snapshot = [&]() {
+      if (snap && k == next_snap && snaps < a.n_ckpt) {
+        c.save(snap + snaps * slot, a.N_max);
+        snaps++;
+        next_snap += a.ckpt_every;
       }
-      if (done) break;
+    };
+    float rx = 0.f, rp = 0.f;
+    if (a.fixed)  // residuals only of the last iteration
+      for (; k + 1 < a.max_iter; k++) {
+        snapshot();
+        c.template iterate<false>(a, eps, rx, rp);
+      }
+    for (bool done = false; !done;) {
+      snapshot();
+      rx = rp = 0.f;
+      c.template iterate<true>(a, eps, rx, rp);
+      k++;
+      c.sum2(rx, rp);
+      done = k >= a.max_iter;
+      if (!__builtin_isfinite(rx + rp)) {
+        st = kNonFinite;
+        done = true;
+      } else if (rx < a.tol && rp < a.tol && (!a.fixed || done)) {
+        st = kConverged;
+        done = true;
+      }
     }
-    if (a.ckpt) lt_save<D>(sX, sP, sZ, Np, a.N_max, a.ckpt + (pt * (a.n_ckpt + 1) + a.n_ckpt) * slot);
+    if (snap) c.save(snap + a.n_ckpt * slot, a.N_max);
 
     // ---- value: g(x_0) + sum <p_j, x_j - x_{j-1}> - delta sum H(x_j, p_j) ----------
-    int lo = (L.lr + 1) * LD;
-    asm volatile("" : "+v"(lo));
-    f4 acc[kLtNT];
-    gemm_nodes<D>(af, sX, L, R, acc);
     float val = 0.f, badf = 0.f;
+    if constexpr (S::kReg)
+      if (c.lr == 0)
 #pragma unroll
-    for (int c = 0; c < kLtNT; c++) {
-      if (c >= NT) continue;
-      const int j = 16 * c + L.lr + 1;
+        for (int ri = 0; ri < S::RPW; ri++) *reinterpret_cast<f4*>(c.sX0 + c.coord(ri)) = c.x0[ri];
+    if constexpr (c.kRows)
+      c.sweep(c.fA, c.imgX, c.tailX, c.X, [&](int t, const f4(&acc)[S::RPW]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const bool ok = L.iok[r] && j <= Np;
-        const int e = lo + 16 * c * LD + L.ic[r];
-        const float xv = sX[e], pv = sP[e], xm = sX[e - LD];
-        const float f = acc[c][r] + eps * tanh_fast(xv);
-        const float term = pv * (xv - xm) - delta * (0.5f * pv * pv - pv * f);
-        val += ok ? term : 0.f;
-        badf += (ok && !(__builtin_isfinite(xv) && __builtin_isfinite(pv))) ? 1.f : 0.f;
-      }
-    }
-    if (L.tid < D) {
+        for (int ri = 0; ri < S::RPW; ri++) {
+          const f4 xm = t > 0 ? c.X[ri][t > 0 ? t - 1 : 0] : row_prev(c.X[ri][NT - 1]) + c.x0_of(ri);
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            // nodes past N have x = p = 0 and add nothing
+            const float xv = c.X[ri][t][r], pv = c.P[ri][t][r];
+            const float f = acc[ri][r] + eps * tanh_fast(xv);
+            val += pv * (xv - xm[r]) - c.delta * (0.5f * pv * pv - pv * f);
+            if (!(__builtin_isfinite(xv) && __builtin_isfinite(pv))) badf = 1.f;
+          }
+        }
+      });
+    __syncthreads();
+    // x_0^T Q x_0 / 2 (the symmetric part of Q is all that counts), a column of Q to a thread
+    for (int i = c.tid; i < D; i += S::kThreads) {
       float qx = 0.f;
-      for (int kq = 0; kq < D; kq++) qx += 0.5f * (a.Q[L.tid * D + kq] + a.Q[kq * D + L.tid]) * sX[kq];
-      val += 0.5f * sX[L.tid] * qx;
-      if (!__builtin_isfinite(sX[L.tid])) badf = 1.f;
+#pragma unroll 10
+      for (int kq = 0; kq < D; kq++) qx += a.Q[kq * D + i] * c.sX0[kq];
+      val += 0.5f * c.sX0[i] * qx;
+      if (!__builtin_isfinite(c.sX0[i])) badf = 1.f;
     }
-    val = wg_sum(val, s_red);
-    badf = wg_sum(badf, s_red + kLtWaves);
+    c.sum2(val, badf);
     if (badf > 0.f || !__builtin_isfinite(val)) st = kNonFinite;
-    if (L.tid == 0) {
+    if (c.tid == 0) {
       if (a.phi) a.phi[pt] = val;
       a.iters[pt] = k;
       a.status[pt] = st;
     }
-    if (a.xtraj || a.ptraj) {
-      const int64_t base = pt * int64_t(a.N_max + 1) * D;
-      for (int e = L.tid; e < (Np + 1) * D; e += kLtThreads) {
-        const int j = e / D, i = e - j * D;
-        if (a.xtraj) a.xtraj[base + e] = sX[j * LD + i];
-        if (a.ptraj) a.ptraj[base + e] = sP[j * LD + i];
+    if constexpr (c.kRows)
+      if (a.xtraj || a.ptraj) {
+        const int64_t base = pt * int64_t(a.N_max + 1) * D;
+#pragma unroll
+        for (int ri = 0; ri < S::RPW; ri++) {
+          if (!c.rows_ok(ri)) continue;
+          const int i0 = c.coord(ri);
+          const f4 x0 = c.x0_of(ri);
+#pragma unroll
+          for (int t = -1; t < NT; t++) {
+            const int j = t < 0 ? 0 : c.node(t);
+            if (t < 0 ? c.lr != 0 : j > c.Np) continue;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+              if (a.xtraj) a.xtraj[base + j * D + i0 + r] = t < 0 ? x0[r] : c.X[ri][t < 0 ? 0 : t][r];
+              if (a.ptraj) a.ptraj[base + j * D + i0 + r] = t < 0 ? 0.f : c.P[ri][t < 0 ? 0 : t][r];
+            }
+          }
+        }
       }
-    }
     __syncthreads();
   }
+}
+
+template <int D, int NT>
+__global__ void __launch_bounds__((LtShape<D, NT>::kThreads), 2) k_lt_forward(LtArgs a) {
+  using S = LtShape<D, NT>;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  __shared__ int s_pt;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (S::kAux && wave == S::RT) lt_forward_wave<D, NT, S::kAux ? kAuxWave : kRowWave>(a, smem, &s_pt);
+  else if (S::kTail && wave == S::RT - 1) lt_forward_wave<D, NT, S::kTail ? kTailWave : kRowWave>(a, smem, &s_pt);
+  else lt_forward_wave<D, NT, kRowWave>(a, smem, &s_pt);
 }
 
 // ---------------------------------------------------------------------------
@@ -588,7 +581,7 @@ template <int D>
 __global__ void __launch_bounds__(kLtThreads, 2) k_lt_backward(LtBwdArgs b) {
   constexpr int LD = D + 1, CT = (D + 15) / 16;
   const LtArgs& a = b.f;
-  extern __shared__ float smem[];
+  extern __shared__ __attribute__((aligned(16))) float smem[];
   __shared__ float s_red[2 * kLtWaves];
   __shared__ float s_wb[4 * 128];  // wbar = M XB_0 (B1): whole sums, or quarters when no wave is idle
   constexpr int kIdleWaves = kLtWaves - (D + 15) / 16;  // waves with no row tile of their own
@@ -1106,14 +1099,35 @@ struct LtState {
 
 typedef const void* KernelPtr;
 
-static KernelPtr forward_kernel(int d) {
-  switch (d) {
-    case 16: return reinterpret_cast<KernelPtr>(&k_lt_forward<16>);
-    case 32: return reinterpret_cast<KernelPtr>(&k_lt_forward<32>);
-    case 100: return reinterpret_cast<KernelPtr>(&k_lt_forward<100>);
-    case 128: return reinterpret_cast<KernelPtr>(&k_lt_forward<128>);
+// Forward kernel for (d, N_max): its column tiles cover N_max.
+struct LtKernel {
+  KernelPtr fn = nullptr;
+  int threads = 0;
+  size_t lds = 0;
+};
+
+template <int D, int NT>
+static LtKernel forward_of() {
+  return {reinterpret_cast<KernelPtr>(&k_lt_forward<D, NT>), LtShape<D, NT>::kThreads,
+          sizeof(float) * LtShape<D, NT>::kLdsFloats};
+}
+template <int D>
+static LtKernel forward_tiles(int N_max) {
+  switch ((N_max + 15) / 16) {
+    case 1: return forward_of<D, 1>();
+    case 2: return forward_of<D, 2>();
+    case 3: return forward_of<D, 3>();
+    default: return forward_of<D, 4>();
   }
-  return nullptr;
+}
+static LtKernel forward_kernel(int d, int N_max) {
+  switch (d) {
+    case 16: return forward_tiles<16>(N_max);
+    case 32: return forward_tiles<32>(N_max);
+    case 100: return forward_tiles<100>(N_max);
+    case 128: return forward_tiles<128>(N_max);
+  }
+  return {};
 }
 
 static KernelPtr backward_kernel(int d) {
@@ -1134,7 +1148,8 @@ static KernelPtr backward_kernel(int d) {
 
 int lt_create(LtState** out, const hjpd_desc& desc) {
   *out = nullptr;
-  if (!forward_kernel(desc.d)) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for d in {16,32,100,128}");
+  const LtKernel fwd = forward_kernel(desc.d, desc.N_max);
+  if (!fwd.fn) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for d in {16,32,100,128}");
   if (desc.N_max > kLtMaxN) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for N_max <= 64");
   LtState* s = new LtState();
   s->d = desc.d;
@@ -1145,8 +1160,7 @@ int lt_create(LtState** out, const hjpd_desc& desc) {
     return hjpd_fail(HJPD_EDEVICE, "device query failed");
   }
   s->n_cu = prop.multiProcessorCount;
-  if (hipFuncSetAttribute(forward_kernel(desc.d), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          int(lt_lds_forward(desc.d, desc.N_max))) != hipSuccess ||
+  if (hipFuncSetAttribute(fwd.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(fwd.lds)) != hipSuccess ||
       hipFuncSetAttribute(backward_kernel(desc.d), hipFuncAttributeMaxDynamicSharedMemorySize,
                           int(lt_lds_backward(desc.d, desc.N_max))) != hipSuccess) {
     delete s;
@@ -1177,10 +1191,10 @@ void lt_destroy(LtState* s) {
   delete s;
 }
 
-static int lt_grid(LtState* st, KernelPtr k, size_t lds) {
+static int lt_grid(LtState* st, KernelPtr k, int threads, size_t lds, int64_t n) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, kLtThreads, lds) != hipSuccess || nb < 1) nb = 1;
-  return nb * st->n_cu;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, threads, lds) != hipSuccess || nb < 1) nb = 1;
+  return int(std::min<int64_t>(int64_t(nb) * st->n_cu, n));
 }
 
 static void fill_args(LtArgs& a, LtState* st, const hjpd_desc& d, int64_t n, const void* x, const void* t,
@@ -1233,11 +1247,11 @@ int lt_solve(LtState* st, const hjpd_desc& d, int64_t n, const void* x, const vo
   LtArgs a;
   fill_args(a, st, d, n, x, t, N, hp, gp, phi, xtraj, ptraj, iters, status, d.max_iter,
             (d.flags & HJPD_FIXED_ITERS) != 0);
-  const size_t lds = lt_lds_forward(d.d, d.N_max);
-  KernelPtr k = forward_kernel(d.d);
+  const LtKernel k = forward_kernel(d.d, d.N_max);
   void* args[] = {&a};
   if (ev0) LT_HIP(hipEventRecord(ev0, s), "hipEventRecord");
-  LT_HIP(hipLaunchKernel(k, dim3(lt_grid(st, k, lds)), dim3(kLtThreads), args, lds, s), "linear-tanh forward");
+  LT_HIP(hipLaunchKernel(k.fn, dim3(lt_grid(st, k.fn, k.threads, k.lds, n)), dim3(k.threads), args, k.lds, s),
+         "linear-tanh forward");
   if (ev1) LT_HIP(hipEventRecord(ev1, s), "hipEventRecord");
   if (launches) *launches = 1;
   if (timing_valid) *timing_valid = ev0 != nullptr;
@@ -1269,7 +1283,7 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
   if (rc) return rc;
   KernelPtr kb = backward_kernel(d.d);
   const size_t lds_b = lt_lds_backward(d.d, d.N_max);
-  const int grid_b = lt_grid(st, kb, lds_b);
+  const int grid_b = lt_grid(st, kb, kLtThreads, lds_b, n);
   rc = grow((void**)&st->seg, &st->seg_bytes, sizeof(float) * size_t(grid_b) * lt_seg_floats(d.d, d.N_max, E));
   if (rc) return rc;
   rc = grow((void**)&st->part, &st->part_bytes, sizeof(float) * size_t(grid_b) * (3 * dd + 1));
@@ -1283,10 +1297,10 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
   a.ckpt = st->ckpt;
   a.ckpt_every = E;
   a.n_ckpt = n_ckpt;
-  KernelPtr kf = forward_kernel(d.d);
-  const size_t lds_f = lt_lds_forward(d.d, d.N_max);
+  const LtKernel kf = forward_kernel(d.d, d.N_max);
   void* fargs[] = {&a};
-  LT_HIP(hipLaunchKernel(kf, dim3(lt_grid(st, kf, lds_f)), dim3(kLtThreads), fargs, lds_f, s), "linear-tanh forward");
+  LT_HIP(hipLaunchKernel(kf.fn, dim3(lt_grid(st, kf.fn, kf.threads, kf.lds, n)), dim3(kf.threads), fargs, kf.lds, s),
+         "linear-tanh forward");
   LtBwdArgs b;
   b.f = a;
   b.f.phi = nullptr;

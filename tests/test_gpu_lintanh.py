@@ -233,3 +233,41 @@ def test_node0_matrix_with_row_exchanges(d):
         v = one["x_traj"][i, 0] + w.tau * two["p_traj"][i, 1]
         bound = (d + 3) * 2.0 ** -24 * (np.abs(M) @ np.abs(v))
         assert np.all(np.abs(two["x_traj"][i, 0] - M @ v) <= bound)
+
+
+def _edge_cases():
+    out = []
+    for d in (16, 32, 100, 128):
+        for N in (1, 2, 15, 16, 17, 32, 33, 48, 49, 64):
+            if d < 128 or N <= 48:  # d = 128 is built for N up to 48
+                out.append((d, N))
+    return out
+
+
+@pytest.mark.parametrize("d,N_max", _edge_cases())
+def test_column_tile_edges_match_oracle(oracle_mod, d, N_max):
+    """Step counts on both sides of the 16-node column tiles, each batch with
+    every step count from N_max down, inputs at an address that is only 4-byte
+    aligned.  FP32 bar 1e-4 against the oracle, values and trajectories."""
+    import torch
+
+    from paper_1803_01215_amd.autograd import LinearTanhValue
+    K, n = 30, min(9, N_max)
+    w = _small_workload(d=d, n=n, N=N_max, K=K, seed=100 + N_max)
+    w.N = np.arange(N_max, N_max - n, -1).astype(np.int32)
+    w.t = np.random.default_rng(N_max).uniform(0.3, 1.2, n)
+    lt = LinearTanhValue(d, N_max, w.sigma, w.tau, K, seed=w.init_seed)
+
+    def odd(a):
+        a = np.asarray(a, np.float32).ravel()
+        buf = torch.empty(a.size + 1, dtype=torch.float32, device="cuda")
+        buf[1:] = torch.tensor(a, device="cuda")
+        return buf[1:]
+
+    out = lt.solver.solve(odd(w.x), odd(w.t), torch.tensor(w.N, device="cuda"), odd(w.hp), odd(w.gp), traj=True)
+    torch.cuda.synchronize()
+    o = _oracle_phi(oracle_mod, w, K, traj=True)
+    assert rel_err(out.phi.cpu().numpy().astype(np.float64), o.phi).max() <= 1e-4
+    for got, want in ((out.x_traj, o.x_traj), (out.p_traj, o.p_traj)):
+        assert traj_err(got.cpu().numpy().astype(np.float64), want, w.N).max() <= 1e-4
+    lt.close()
