@@ -13,13 +13,9 @@
 // counter; the kernel is compiled for one to four 16-node column tiles.
 //
 // Reverse mode (hjpd_value_grad): the forward pass stores the state every E
-// iterations; the backward kernel, per point, recomputes each segment of E
-// iterations from its checkpoint into a per-workgroup buffer (x^k and the new
-// multipliers p^{k+1}), then applies the transposed Jacobian of each iteration
-// (vector-Jacobian product) from the last iteration down to the first.  The
-// VJP's dense products A xbar and A^T vbar reuse the forward fragments; the
-// parameter gradient dA = sum of outer products over nodes is an MFMA product
-// accumulated in registers; dM and the direct dQ term are rank-1 VALU updates.
+// iterations; the reverse kernel (k_lt_backward; the step is hjpd_lt_back.hpp's)
+// recomputes each segment from its checkpoint and applies the transposed
+// Jacobian of every iteration from the last one down.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -27,397 +23,12 @@
 #include <type_traits>
 #include <vector>
 
-#include "hjpd_lt_core.hpp"
+#include "hjpd_lt_back.hpp"
 
 namespace hjpd {
 
-constexpr int kLtThreads = 512;
-constexpr int kLtWaves = kLtThreads / 64;
 constexpr int kLtCounters = 8;
-constexpr int kLtNT = 4;                                                    // 16-node column tiles: up to 64 nodes
-
-// LDS rows per array: nodes 0 .. 16*NT + 1 (NT column tiles of 16 nodes), so
-// every GEMM column read and every j+1 read stays inside the array.
-__host__ __device__ constexpr int lt_rows(int N_max) { return 16 * ((N_max + 15) / 16) + 2; }
-inline size_t lt_lds_backward(int d, int N_max) { return size_t(5) * lt_rows(N_max) * (d + 1) * sizeof(float); }
-// Per-workgroup reverse-mode buffer (floats): E recomputed steps of (x^k, p^{k+1}) in the LDS layout,
-// the saved adjoint (3 arrays), and E staged (XB_0, w) pairs for dM.
-__host__ __device__ inline int64_t lt_seg_floats(int d, int N_max, int E) {
-  const int64_t CK = int64_t(N_max + 1) * d, RL = int64_t(lt_rows(N_max)) * (d + 1);
-  return int64_t(E) * 2 * RL + 3 * CK + int64_t(E) * 2 * d;
-}
-
-struct LtBwdArgs {
-  LtArgs f;
-  const float* grad_phi;  // [n]
-  float* dphi_dx;         // [n][d]
-  float* seg;             // per workgroup: E snapshots of (x^k, p^{k+1}) + adjoint save area
-  float* part;            // per workgroup: dA (d*d), dM (d*d), dQ direct (d*d), deps (1)
-  int K;
-};
-
-// Per-thread constants of the accumulator layout.
-template <int D>
-struct LtLane {
-  static constexpr int KS = D / 4, RT = (D + 15) / 16, LD = D + 1;
-  int tid, wave, lr, lk;
-  bool has;
-  int ic[4];
-  bool iok[4];
-  __device__ LtLane() {
-    tid = threadIdx.x;
-    wave = tid >> 6;
-    const int lane = tid & 63;
-    lr = lane & 15;
-    lk = lane >> 4;
-    has = wave < RT;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int i = 16 * wave + 4 * lk + r;
-      iok[r] = has && i < D;
-      ic[r] = iok[r] ? i : D;  // rows past d land on the padding column
-    }
-  }
-};
-
-// Reduce a float over the workgroup (all threads get the total).
-__device__ __forceinline__ float wg_sum(float v, float* s_red) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s_red[wave] = v;
-  __syncthreads();
-  float t = 0.f;
-#pragma unroll
-  for (int w = 0; w < kLtWaves; w++) t += s_red[w];
-  return t;
-}
-
-// acc[c] = rows of this wave x nodes 16c+1 .. 16c+16:  sum_k frag[row][k] B[node][k],
-// for all kLtNT column tiles (a fixed count keeps the MFMA chain free of
-// branches).  Node rows at or past R (the array's row count) read row R-1,
-// which is zero (every array is zero past N); those columns are not used.
-template <int D>
-__device__ __forceinline__ void gemm_nodes(const float (&frag)[D / 4], const float* sB, const LtLane<D>& L, int R,
-                                           f4 (&acc)[kLtNT]) {
-  constexpr int LD = D + 1;
-  int base[kLtNT];
-#pragma unroll
-  for (int c = 0; c < kLtNT; c++) {
-    const int row = 16 * c + L.lr + 1;
-    base[c] = (row < R ? row : R - 1) * LD + L.lk;
-    asm volatile("" : "+v"(base[c]));
-    acc[c] = f4{0.f, 0.f, 0.f, 0.f};
-  }
-  // Scheduling fence after every k-step: the scheduler cannot hoist B reads
-  // ahead of earlier k-steps' MFMAs (each hoisted read holds a VGPR).  A fence
-  // every second or fourth step measured slower in both kernels.
-#pragma unroll
-  for (int s = 0; s < D / 4; s++) {
-#pragma unroll
-    for (int c = 0; c < kLtNT; c++) acc[c] = mfma4(frag[s], sB[base[c] + 4 * s], acc[c]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// out[ct] += sum_{j in [jlo, jhi]} scale U[j][row] V[j][col] for this wave's 16
-// rows and column tiles ct (16 columns each): outer products summed over nodes.
-template <int D>
-__device__ __forceinline__ void gemm_outer(const LtLane<D>& L, const float* sU, const float* sV, float scale, int jlo,
-                                           int jhi, f4 (&out)[(D + 15) / 16]) {
-  constexpr int LD = D + 1, CT = (D + 15) / 16;
-  const int row = 16 * L.wave + L.lr;
-  const int rc = (L.has && row < D) ? row : D;
-  // two k-steps per trip, all of their LDS reads issued before the products;
-  // the second step of the last trip runs only if it has nodes
-  for (int j0 = jlo; j0 <= jhi; j0 += 8) {
-    float a[2], b[2][CT];
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-      const int j = j0 + 4 * h + L.lk;
-      const bool ok = j <= jhi;
-      const int jr = ok ? j : jlo;
-      a[h] = ok ? scale * sU[jr * LD + rc] : 0.f;
-#pragma unroll
-      for (int ct = 0; ct < CT; ct++) {
-        const int col = 16 * ct + L.lr;
-        b[h][ct] = sV[jr * LD + (col < D ? col : D)];
-      }
-    }
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) out[ct] = mfma4(a[0], b[0][ct], out[ct]);
-    if (j0 + 4 <= jhi) {
-#pragma unroll
-      for (int ct = 0; ct < CT; ct++) out[ct] = mfma4(a[1], b[1][ct], out[ct]);
-    }
-  }
-}
-
-// One iteration of the splitting (dual, node 0, primal, extrapolation) on the
-// LDS state.  If sx_out / sp_out are given, x^k (before the iteration) and
-// p^{k+1} (after the dual step) are stored there ([N+1][d], row stride d).
-// Adds this thread's partial residual sums to rx, rp.
-template <int D, bool kReuseTanh = false>
-__device__ void lt_iterate(const LtLane<D>& L, const LtArgs& a, const float (&af)[D / 4], const float (&atf)[D / 4],
-                           float* sX, float* sP, float* sZ, int Np, int NT, float delta, float eps, float* sx_out,
-                           float* sp_out, float& rx, float& rp) {
-  constexpr int LD = D + 1;
-  const int R = lt_rows(a.N_max);
-  const float sigma = a.sigma, tau = a.tau, theta = a.theta;
-  const float lam = sigma * delta, c1 = 1.f / (1.f + lam), td = tau * delta;
-  int lo = (L.lr + 1) * LD;
-  asm volatile("" : "+v"(lo));
-  if (sx_out)
-    for (int e = L.tid; e < (Np + 1) * LD; e += kLtThreads) sx_out[e] = sX[e];
-  // ---- dual step: p_j <- (p_j + sigma (z_j - z_{j-1}) + lam f_j) c1 ----------
-  f4 acc[kLtNT];
-  // With kReuseTanh the dual step keeps tanh(x_j) for the primal step (x is
-  // unchanged until then): faster in the reverse sweep's recompute, slower in
-  // the forward kernel, whose 128 registers then spill more.
-  f4 thc[kLtNT];
-  gemm_nodes<D>(af, sX, L, R, acc);
-#pragma unroll
-  for (int c = 0; c < kLtNT; c++) {
-    thc[c] = f4{0.f, 0.f, 0.f, 0.f};
-    if (c >= NT) continue;
-    const int j = 16 * c + L.lr + 1;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const bool ok = L.iok[r] && j <= Np;
-      const int e = lo + 16 * c * LD + L.ic[r];
-      const float xv = sX[e], pv = sP[e];
-      const float v = pv + sigma * (sZ[e] - sZ[e - LD]);
-      const float thd = tanh_fast(xv);
-      if constexpr (kReuseTanh) thc[c][r] = thd;
-      const float f = acc[c][r] + eps * thd;
-      const float pn = (v + lam * f) * c1;
-      const float dp = pn - pv;
-      rp += ok ? dp * dp : 0.f;
-      sP[e] = ok ? pn : pv;
-    }
-  }
-  __syncthreads();
-  if (sp_out)
-    for (int e = L.tid; e < (Np + 1) * LD; e += kLtThreads) sp_out[e] = sP[e];
-  // ---- node 0 (VALU): x_0 <- M (x_0 + tau p_1), M symmetric, read by columns.
-  // The four lanes of a quad share output i = tid / 4, each summing a quarter
-  // of its terms, and add the quarters with two quad exchanges (the forward
-  // kernel and the reverse kernel's recompute use this same summation order,
-  // so the recompute reproduces the forward bit for bit).
-  float x0n = 0.f, z0n = 0.f;
-  const int i0 = L.tid >> 2, q0 = L.tid & 3;
-  // With d up to 112, half of M's terms are loaded before the primal product
-  // and the rest after it, and all are summed after it, so part of their
-  // latency overlaps the product (loading all of them first spills registers);
-  // at d = 128 that measured slower, and the sum runs before the product.
-  constexpr int KQ = (D + 3) / 4;
-  if constexpr (D <= 112) {
-    // Quads past row d load row d - 1 and discard the sum.  The opaque column
-    // keeps the loads in the iteration.
-    int col = i0 < D ? i0 : D - 1;
-    asm volatile("" : "+v"(col));
-    constexpr int KP = KQ / 2;  // terms loaded ahead of the product
-    float mv[KQ];
-#pragma unroll
-    for (int s = 0; s < KP; s++) {
-      const int kq = q0 * KQ + s;
-      mv[s] = (4 * KQ == D || kq < D) ? a.M[kq * D + col] : 0.f;
-    }
-    // ---- primal step, j = 1..N-1, with G = A^T P: the product ---------------------
-    gemm_nodes<D>(atf, sP, L, R, acc);
-#pragma unroll
-    for (int s = KP; s < KQ; s++) {
-      const int kq = q0 * KQ + s;
-      mv[s] = (4 * KQ == D || kq < D) ? a.M[kq * D + col] : 0.f;
-    }
-    float part = 0.f;
-#pragma unroll
-    for (int s = 0; s < KQ; s++) {
-      const int kq = q0 * KQ + s;
-      if (4 * KQ == D || kq < D) part += mv[s] * (sX[kq] + tau * sP[LD + kq]);
-    }
-    part += dpp_f<kDppQuad1032>(part);
-    part += dpp_f<kDppQuad2301>(part);
-    if (i0 < D && q0 == 0) {
-      const float old = sX[i0];
-      const float dx = part - old;
-      rx += dx * dx;
-      x0n = part;
-      z0n = part + theta * dx;
-    }
-  } else {
-    // opaque column index: the loop-invariant loads of M stay in the iteration
-    int col = i0;
-    asm volatile("" : "+v"(col));
-    float part = 0.f;
-    if (i0 < D) {
-#pragma unroll
-      for (int s = 0; s < KQ; s++) {
-        const int kq = q0 * KQ + s;
-        if (kq < D) part += a.M[kq * D + col] * (sX[kq] + tau * sP[LD + kq]);
-      }
-    }
-    part += dpp_f<kDppQuad1032>(part);
-    part += dpp_f<kDppQuad2301>(part);
-    if (i0 < D && q0 == 0) {
-      const float old = sX[i0];
-      const float dx = part - old;
-      rx += dx * dx;
-      x0n = part;
-      z0n = part + theta * dx;
-    }
-    // ---- primal step, j = 1..N-1, with G = A^T P: the product ---------------------
-    gemm_nodes<D>(atf, sP, L, R, acc);
-  }
-  // ---- primal step: the update ----------------------------------------------------
-#pragma unroll
-  for (int c = 0; c < kLtNT; c++) {
-    if (c >= NT) continue;
-    const int j = 16 * c + L.lr + 1;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const bool ok = L.iok[r] && j <= Np - 1;
-      const int e = lo + 16 * c * LD + L.ic[r];
-      const float xv = sX[e], pv = sP[e], pp = sP[e + LD], zv = sZ[e];
-      const float th = kReuseTanh ? thc[c][r] : tanh_fast(xv);
-      const float gx = acc[c][r] + eps * (1.f - th * th) * pv;  // -grad_x H
-      const float xn = xv - tau * (pv - pp) - td * gx;
-      const float dx = xn - xv;
-      rx += ok ? dx * dx : 0.f;
-      sZ[e] = ok ? xn + theta * dx : zv;
-      sX[e] = ok ? xn : xv;
-    }
-  }
-  __syncthreads();
-  if (i0 < D && q0 == 0) {
-    sX[i0] = x0n;
-    sZ[i0] = z0n;
-  }
-  __syncthreads();
-}
-
-// Random start (section 6 set-up) into LDS; rows past N and the padding column zero.
-template <int D>
-__device__ void lt_init(const LtArgs& a, int64_t pt, int Np, int R, float* sX, float* sP, float* sZ) {
-  constexpr int LD = D + 1;
-  for (int e = threadIdx.x; e < R * LD; e += kLtThreads) {
-    const int j = e / LD, i = e - j * LD;
-    float xv = 0.f, pv = 0.f;
-    if (j <= Np && i < D) {
-      const float xt = a.x[pt * D + i];
-      xv = (j < Np) ? float(double(xt) + start_noise(a.seed, uint64_t(pt), kArrX, j, i)) : xt;
-      pv = (j >= 1) ? float(start_noise(a.seed, uint64_t(pt), kArrP, j, i)) : 0.f;
-    }
-    sX[e] = xv;
-    sZ[e] = xv;
-    sP[e] = pv;
-  }
-  __syncthreads();
-}
-
-// Copy LDS arrays (row stride d+1) to a compact global snapshot (row stride d).
-template <int D>
-__device__ void lt_save(const float* sX, const float* sP, const float* sZ, int Np, int N_max, float* dst) {
-  constexpr int LD = D + 1;
-  const int64_t CK = int64_t(N_max + 1) * D;
-  for (int e = threadIdx.x; e < (Np + 1) * D; e += kLtThreads) {
-    const int j = e / D, i = e - j * D;
-    dst[e] = sX[j * LD + i];
-    dst[CK + e] = sP[j * LD + i];
-    dst[2 * CK + e] = sZ[j * LD + i];
-  }
-  __syncthreads();
-}
-
-// Load up to three consecutive snapshot arrays into LDS (zero past N and in the
-// padding column); null targets are skipped.  The loads of one array are
-// issued together before their LDS stores (one memory latency per array and
-// call, not one per element).
-template <int D>
-__device__ void lt_load(float* s0, float* s1, float* s2, int Np, int N_max, int R, const float* src) {
-  constexpr int LD = D + 1;
-  constexpr int NL = (lt_rows(kLtMaxN) * LD + kLtThreads - 1) / kLtThreads;
-  const int64_t CK = int64_t(N_max + 1) * D;
-  float* dst[3] = {s0, s1, s2};
-  // opaque thread index: the per-element row/column divisions below are
-  // recomputed per call instead of being hoisted and held for the kernel
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-#pragma unroll
-  for (int q = 0; q < 3; q++) {
-    if (!dst[q]) continue;
-    const float* sq = src + q * CK;
-    float v[NL];
-#pragma unroll
-    for (int u = 0; u < NL; u++) {
-      const int e = tid + u * kLtThreads;
-      const int j = e / LD, i = e - j * LD;
-      const bool ok = e < R * LD && j <= Np && i < D;
-      v[u] = ok ? sq[j * D + i] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < NL; u++) {
-      const int e = tid + u * kLtThreads;
-      if (e < R * LD) dst[q][e] = v[u];
-    }
-  }
-  __syncthreads();
-}
-
-// Rows 0..N of two arrays stored in the LDS layout (src, src + RL), read into
-// registers by lt_rows_load and written to LDS by lt_rows_store; rows past N
-// already hold zero there.  Every thread issues its loads together and no
-// branch guards them: indices past row N are clamped to the last entry of row
-// N, which those threads then write with its own value.
-template <int D>
-constexpr int lt_rows_per_thread() { return (lt_rows(kLtMaxN) * (D + 1) + kLtThreads - 1) / kLtThreads; }
-
-template <int D>
-__device__ __forceinline__ void lt_rows_load(const float* src, int64_t RL, int Np, float (&v)[2][lt_rows_per_thread<D>()]) {
-  constexpr int NL = lt_rows_per_thread<D>();
-  const int last = (Np + 1) * (D + 1) - 1;
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-#pragma unroll
-  for (int q = 0; q < 2; q++)
-#pragma unroll
-    for (int u = 0; u < NL; u++) v[q][u] = src[q * RL + min(tid + u * kLtThreads, last)];
-}
-
-template <int D>
-__device__ __forceinline__ void lt_rows_store(float* s0, float* s1, int Np, const float (&v)[2][lt_rows_per_thread<D>()]) {
-  constexpr int NL = lt_rows_per_thread<D>();
-  const int last = (Np + 1) * (D + 1) - 1;
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-#pragma unroll
-  for (int u = 0; u < NL; u++) {
-    const int e = min(tid + u * kLtThreads, last);
-    s0[e] = v[0][u];
-    s1[e] = v[1][u];
-  }
-}
-
-template <int D>
-__device__ bool lt_bad_input(const LtArgs& a, int64_t pt) {
-  const int Np = a.N[pt];
-  const float tt = a.t[pt];
-  bool bad = !(tt > 0.f) || !__builtin_isfinite(tt) || Np < 1 || Np > a.N_max;
-  for (int i = 0; i < D && !bad; i++) bad = !__builtin_isfinite(a.x[pt * D + i]);
-  return bad;
-}
-
-template <int D>
-__device__ void lt_load_fragments(const float* A, int wave, int lr, int lk, float (&af)[D / 4], float (&atf)[D / 4]) {
-  const int row = 16 * wave + lr;
-#pragma unroll
-  for (int s = 0; s < D / 4; s++) {
-    const int k = 4 * s + lk;
-    af[s] = row < D ? A[row * D + k] : 0.f;
-    atf[s] = row < D ? A[k * D + row] : 0.f;
-  }
-}
+constexpr int kLtPackBlocks = 16;
 
 // t > 0, 1 <= N <= N_max, x finite; the whole wave calls it for one point.
 template <int D>
@@ -496,7 +107,7 @@ __device__ __forceinline__ void lt_forward_wave(const LtArgs& a, float* smem, in
     if constexpr (S::kReg)
       if (c.lr == 0)
 #pragma unroll
-        for (int ri = 0; ri < S::RPW; ri++) *reinterpret_cast<f4*>(c.sX0 + c.coord(ri)) = c.x0[ri];
+        for (int ri = 0; ri < S::RPW; ri++) st4(c.sX0 + c.coord(ri), c.x0[ri]);
     if constexpr (c.kRows)
       c.sweep(c.fA, c.imgX, c.tailX, c.X, [&](int t, const f4(&acc)[S::RPW]) __attribute__((always_inline)) {
 #pragma unroll
@@ -563,395 +174,326 @@ __global__ void __launch_bounds__((LtShape<D, NT>::kThreads), 2) k_lt_forward(Lt
   else lt_forward_wave<D, NT, kRowWave>(a, smem, &s_pt);
 }
 
-// ---------------------------------------------------------------------------
-// Reverse sweep.  Adjoint arrays XB, PB, ZB (of x, p, z after an iteration)
-// live in LDS; per iteration k (from K-1 down to 0), with x^k in S0 and
-// p^{k+1} in S1, the transposed Jacobian of the iteration is applied:
-//   z' = x' + theta (x' - x)        XB += (1+theta) ZB;  Xpre = -theta ZB   (z'_N = x_N: Xpre_N = ZB_N + XB_N)
-//   x'_0 = M w, w = x_0 + tau p'_1  wbar = M XB_0;  Xpre_0 += wbar;  PB_1 += tau wbar;  dM += XB_0 w^T
-//   x'_j = x_j - tau (p'_j - p'_{j+1}) - tau delta (A^T p'_j + eps (1 - th_j^2) p'_j),  j < N:
-//        Xpre_j += XB_j + 2 tau delta eps (1 - th_j^2) th_j p'_j XB_j
-//        PB_j += -tau XB_j - tau delta (A XB)_j - tau delta eps (1 - th_j^2) XB_j + tau XB_{j-1}
-//        dA += -tau delta p'_j XB_j^T;  deps += -tau delta sum (1 - th^2) p' XB
-//   p'_j = c1 (p_j + sigma (z_j - z_{j-1}) + lam (A x_j + eps th_j)):
-//        vbar = c1 PB;  Ppre = vbar;  Zpre_j = sigma (vbar_j - vbar_{j+1})
-//        Xpre_j += lam (A^T vbar)_j + lam eps (1 - th_j^2) vbar_j;  dA += lam vbar_j x_j^T;  deps += lam th vbar
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kLtThreads, 2) k_lt_backward(LtBwdArgs b) {
-  constexpr int LD = D + 1, CT = (D + 15) / 16;
+template <int D, int NT, int KIND>
+__device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem) {
+  using C = LtBack<D, NT, KIND>;
+  using S = typename C::S;
+  constexpr int RPW = C::RPW, RT = C::RT, LD = D + 1;
+  constexpr int64_t DD = int64_t(D) * D, TF = C::tiles_floats();
   const LtArgs& a = b.f;
-  extern __shared__ __attribute__((aligned(16))) float smem[];
-  __shared__ float s_red[2 * kLtWaves];
-  __shared__ float s_wb[4 * 128];  // wbar = M XB_0 (B1): whole sums, or quarters when no wave is idle
-  constexpr int kIdleWaves = kLtWaves - (D + 15) / 16;  // waves with no row tile of their own
-  auto wbar = [&](int i) {
-    if constexpr (kIdleWaves > 0) return s_wb[i];
-    else return (s_wb[i] + s_wb[128 + i]) + (s_wb[256 + i] + s_wb[384 + i]);
-  };
-  const LtLane<D> L;
-  const int R = lt_rows(a.N_max);
-  const int NT = (a.N_max + 15) / 16;
-  float* S0 = smem;
-  float* S1 = S0 + R * LD;
-  float* S2 = S1 + R * LD;
-  float* S3 = S2 + R * LD;
-  float* S4 = S3 + R * LD;
-  const float eps = a.hp[0];
-  const float sigma = a.sigma, tau = a.tau, theta = a.theta;
-  float af[D / 4], atf[D / 4];
-  lt_load_fragments<D>(a.hp + 1, L.wave, L.lr, L.lk, af, atf);
-  f4 dA[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++) dA[ct] = f4{0.f, 0.f, 0.f, 0.f};
-  float deps = 0.f;
-  // dM and the direct dQ term accumulate in this workgroup's partial block in
-  // global memory, in the accumulator layout (wave rows x column tiles), so no
-  // per-thread d*d/threads arrays or index divisions stay live in registers.
-  const int64_t DD = int64_t(D) * D;
-  float* part = b.part + int64_t(blockIdx.x) * (3 * DD + 1);
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int row = 16 * L.wave + 4 * L.lk + r, col = 16 * ct + L.lr;
-      if (L.has && row < D && col < D) {
-        part[DD + row * D + col] = 0.f;
-        part[2 * DD + row * D + col] = 0.f;
-      }
-    }
-
+  C c;
+  c.setup_back(a, smem);
+  const int tid = c.tid, lr = c.lr, lk = c.lk;
+  const float eps = a.hp[0], tau = a.tau;
   const int E = a.ckpt_every;
-  const int64_t CK = int64_t(a.N_max + 1) * D;
-  const int64_t slot = 3 * CK;
-  const int64_t RL = int64_t(R) * LD;  // a recomputed x^k or p^{k+1}, in the LDS layout
-  float* segx = b.seg + int64_t(blockIdx.x) * lt_seg_floats(D, a.N_max, E);
-  float* adjsave = segx + int64_t(E) * 2 * RL;
-  float* stage = adjsave + 3 * CK;  // per step of a segment: XB_0 (node-0 adjoint) and w = x_0 + tau p'_1
+  const int64_t CK = int64_t(a.N_max + 1) * D, slot = 3 * CK;
+  float* seg = b.seg + int64_t(blockIdx.x) * (int64_t(E) * (2 * TF + 2 * D) + 2 * TF);
+  float* adj = seg + int64_t(E) * 2 * TF;
+  float* stage = adj + 2 * TF;  // per step of a segment: XB_0 and w = x_0 + tau p'_1
+  // dA is summed in registers; the direct dQ term and (d > 32) dM in this
+  // workgroup's partial block
+  float* part = b.part + int64_t(blockIdx.x) * (3 * DD + 1);
+  for (int e = tid; e < DD; e += S::kThreads) part[DD + e] = part[2 * DD + e] = 0.f;
+  __syncthreads();
 
   // Points are dealt to the workgroups in a fixed order (every point costs
   // the same K iterations), so each workgroup's partial sums of dA, dM, dQ and
   // deps, and with them the gradients, are the same from call to call.
   for (int64_t pt = blockIdx.x; pt < a.n; pt += gridDim.x) {
     const float w = b.grad_phi[pt];
-    if (lt_bad_input<D>(a, pt) || w == 0.f) {
-      for (int i = L.tid; i < D; i += kLtThreads) b.dphi_dx[pt * D + i] = 0.f;
+    if (w == 0.f || lt_bad_point<D>(a, pt)) {
+      for (int i = tid; i < D; i += S::kThreads) b.dphi_dx[pt * D + i] = 0.f;
       continue;
     }
-    const int Np = a.N[pt];
-    const float delta = a.t[pt] / float(Np), lam = sigma * delta, c1 = 1.f / (1.f + lam), td = tau * delta;
+    c.set_point(a, pt);
     const float* ck_pt = a.ckpt + pt * (a.n_ckpt + 1) * slot;
+    f4 xb0[RPW], zb0[RPW];  // node 0's adjoints (d <= 32)
+    float s1 = 0.f, s2 = 0.f;
 
-    // ---- adjoint of the value at the final iterate ---------------------------------
-    float* XB = S2;
-    float* PB = S3;
-    float* ZB = S4;
-    lt_load<D>(S0, S1, nullptr, Np, a.N_max, R, ck_pt + a.n_ckpt * slot);
+    // ---- adjoint of the value at the final iterate: XB, PB; dA += w delta sum p_j x_j^T ----
     {
-      int lo = (L.lr + 1) * LD;
-      asm volatile("" : "+v"(lo));
-      f4 ax[kLtNT], atp[kLtNT];
-      gemm_nodes<D>(af, S0, L, R, ax);
-      gemm_nodes<D>(atf, S1, L, R, atp);
-      for (int e = L.tid; e < R * LD; e += kLtThreads) {
-        XB[e] = 0.f;
-        PB[e] = 0.f;
-        ZB[e] = 0.f;
-      }
-      __syncthreads();
+      const float* last = ck_pt + a.n_ckpt * slot;
+      const float wd = w * c.delta;
+      for (int i = tid; i < D; i += S::kThreads) c.sX0[i] = last[i];
+      if constexpr (C::kRows) {
+        c.load_nodes(last, c.X);
+        c.load_nodes(last + CK, c.P);
 #pragma unroll
-      for (int c = 0; c < kLtNT; c++) {
-        if (c >= NT) continue;
-        const int j = 16 * c + L.lr + 1;
+        for (int ri = 0; ri < RPW; ri++) {
+          if (lr == 0 && c.rows_ok(ri)) st4(c.sV + c.coord(ri), c.P[ri][0]);
+          if constexpr (!S::kReg)
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const bool ok = L.iok[r] && j <= Np;
-          const int e = lo + 16 * c * LD + L.ic[r];
-          const float xv = S0[e], pv = S1[e], xm = S0[e - LD];
-          const float pn = (j < Np) ? S1[e + LD] : 0.f;
-          const float th = tanh_fast(xv);
-          const float gx = pv - pn + delta * (atp[c][r] + eps * (1.f - th * th) * pv);
-          const float gp = xv - xm + delta * (ax[c][r] + eps * th - pv);
-          if (ok) {
-            XB[e] = w * gx;
-            PB[e] = w * gp;
-          }
-          deps += ok ? w * delta * pv * th : 0.f;
+            for (int t = 0; t < NT; t++) {
+              c.put(c.imgX, c.tailX, t, c.X[0][t]);
+              c.put(c.imgP, c.tailP, t, c.P[0][t]);
+              c.put(c.img3, nullptr, t, wd * c.X[0][t]);
+            }
         }
       }
-      if (L.tid < D) {
-        float qx = 0.f;
-        for (int kq = 0; kq < D; kq++) qx += 0.5f * (a.Q[L.tid * D + kq] + a.Q[kq * D + L.tid]) * S0[kq];
-        XB[L.tid] = w * (qx - S1[LD + L.tid]);
-      }
-      // dQ (direct) += w x_0 x_0^T / 2 ; dA += w delta sum_j p_j x_j^T
-      {
-        // opaque per-lane base: keeps the 28 addresses from being hoisted
-        // out of the point loop (and held in registers for the whole kernel)
-        int rb = 16 * L.wave + 4 * L.lk;
-        asm volatile("" : "+v"(rb));
-        float* pq = part + 2 * DD + int64_t(rb) * D + L.lr;
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = rb + r, col = 16 * ct + L.lr;
-            if (L.has && row < D && col < D) pq[r * D + 16 * ct] += 0.5f * w * S0[row] * S0[col];
-          }
-      }
-      gemm_outer<D>(L, S1, S0, w * delta, 1, Np, dA);
       __syncthreads();
+      for (int i = tid; i < D; i += S::kThreads) {
+        float qx = 0.f;
+#pragma unroll 10
+        for (int k = 0; k < D; k++) qx += a.Qs[k * D + i] * c.sX0[k];
+        const float xb = w * (qx - c.sV[i]);
+        c.sXb0[i] = c.sE[i] = xb;
+        c.sZb0[i] = 0.f;
+      }
+      for (int e = tid; e < DD; e += S::kThreads) part[2 * DD + e] += 0.5f * w * c.sX0[e / D] * c.sX0[e % D];
+      if constexpr (C::kRows) {
+        float sp = 0.f;
+        c.load_matrices(a);
+        c.sweep(c.fA, c.imgX, c.tailX, c.X, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
+          const float wj = c.node(t) <= c.Np ? w : 0.f;
+#pragma unroll
+          for (int ri = 0; ri < RPW; ri++) {
+            f4 x0 = f4{0.f, 0.f, 0.f, 0.f}, pb;
+            if (t == 0 && lr == 0 && c.rows_ok(ri)) x0 = ld4(c.sX0 + c.coord(ri));
+            const f4 xm = t > 0 ? c.X[ri][t > 0 ? t - 1 : 0] : row_prev(c.X[ri][NT - 1]) + x0;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+              const float xv = c.X[ri][t][r], pv = c.P[ri][t][r], th = tanh_fast(xv);
+              pb[r] = wj * (xv - xm[r] + c.delta * (acc[ri][r] + eps * th - pv));
+              sp += pv * th;
+            }
+            if constexpr (S::kPbLds) st4(at<true>(c.sPb, 4 * tid) + 256 * RT * t, pb);
+            else c.PB[ri][t] = pb;
+          }
+        });
+        c.deps += wd * sp;
+        c.sweep(c.fAt, c.imgP, c.tailP, c.P, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int ri = 0; ri < RPW; ri++) {
+            const f4 pn = t < NT - 1 ? c.P[ri][t < NT - 1 ? t + 1 : t] : row_next(c.P[ri][0]);
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+              const float pv = c.P[ri][t][r], th = tanh_fast(c.X[ri][t][r]);
+              c.ZB[ri][t][r] = w * (pv - pn[r] + c.delta * (acc[ri][r] + eps * ((1.f - th * th) * pv)));
+              c.XB[ri][t][r] = 0.f;
+            }
+          }
+        });
+        if constexpr (S::kReg) {
+#pragma unroll
+          for (int ri = 0; ri < RPW; ri++)
+#pragma unroll
+            for (int t = 0; t < NT; t++) {
+              c.scratch_put(0, ri, t, c.P[ri][t]);
+              c.scratch_put(1, ri, t, wd * c.X[ri][t]);
+            }
+          c.outer_scratch();
+        } else {
+          c.outer(c.imgP, c.img3);
+        }
+      }
+      __syncthreads();
+      if constexpr (S::kReg) {
+#pragma unroll
+        for (int ri = 0; ri < RPW; ri++) {
+          xb0[ri] = zb0[ri] = f4{0.f, 0.f, 0.f, 0.f};
+          if (lr == 0) xb0[ri] = ld4(c.sXb0 + c.coord(ri));
+        }
+      } else if constexpr (!S::kAux || KIND == kAuxWave) {
+        c.node0_product();
+      }
     }
 
     // ---- segments, last to first ------------------------------------------------------
     const int nseg = (b.K + E - 1) / E;
     for (int sg = nseg - 1; sg >= 0; sg--) {
-      const int k0 = sg * E, k1 = min(b.K, k0 + E);
+      const int k0 = sg * E, nk = min(b.K, k0 + E) - k0;
       // save the adjoint, recompute the segment forward from its checkpoint
-      lt_save<D>(XB, PB, ZB, Np, a.N_max, adjsave);
-      lt_load<D>(S0, S1, S2, Np, a.N_max, R, ck_pt + sg * slot);
-      for (int k = k0; k < k1; k++) {
+      if constexpr (C::kRows) {
+        c.store_tiles(adj, c.XB);
+        c.store_tiles(adj + TF, c.ZB);
+      }
+      c.load_snapshot(ck_pt + sg * slot, a.N_max);
+      if constexpr (C::kRows) c.load_matrices(a);
+      c.put_all(c.imgX, c.tailX, c.X);
+      for (int k = 0; k < nk; k++) {
+        float* q = seg + int64_t(k) * 2 * TF;
+        float* st = stage + int64_t(k) * 2 * D;
         float rx = 0.f, rp = 0.f;
-        float* so = segx + int64_t(k - k0) * 2 * RL;
-        lt_iterate<D, true>(L, a, af, atf, S0, S1, S2, Np, NT, delta, eps, so, so + RL, rx, rp);
-      }
-      XB = S2;
-      PB = S3;
-      ZB = S4;
-      lt_load<D>(XB, PB, ZB, Np, a.N_max, R, adjsave);
-      // reverse sweep through the segment
-      // x^k and p^{k+1} of each step are loaded into registers during the
-      // previous step's last outer product and written to LDS at the step's
-      // start (read after the barrier that ends (A))
-      float rows[2][lt_rows_per_thread<D>()];
-      lt_rows_load<D>(segx + int64_t(k1 - 1 - k0) * 2 * RL, RL, Np, rows);
-      for (int k = k1 - 1; k >= k0; k--) {
-        lt_rows_store<D>(S0, S1, Np, rows);
-        int lo = (L.lr + 1) * LD;
-        asm volatile("" : "+v"(lo));
-        // (A) extrapolation
-        // branch-free: the padding column holds zero in both arrays and stays
-        // zero (0 - theta * 0 = +0), row N's x-adjoint is written back unchanged
-        for (int e = L.tid; e < (Np + 1) * LD; e += kLtThreads) {
-          const int j = e / LD;
-          const float zb = ZB[e], xb = XB[e];
-          const bool mid = j < Np;
-          XB[e] = mid ? xb + (1.f + theta) * zb : xb;
-          ZB[e] = mid ? 0.f - theta * zb : zb + xb;
+        f4 x0[RPW];
+        if constexpr (C::kRows) {
+          c.store_tiles(q, c.X);
+          if constexpr (!S::kAux)
+#pragma unroll
+            for (int ri = 0; ri < RPW; ri++) x0[ri] = c.x0_of(ri);
         }
-        __syncthreads();
-        f4 thk[kLtNT];  // tanh(x_j^k): formed in (B2), used again in (C2)
+        c.template iterate<false>(a, eps, rx, rp);
+        if constexpr (S::kAux && KIND == kAuxWave)
+          for (int i = tid & 63; i < D; i += 64) st[D + i] = c.sW[i];
+        if constexpr (C::kRows) {
+          c.store_tiles(q + TF, c.P);
+          if constexpr (!S::kAux)
+            if (lr == 0)
 #pragma unroll
-        for (int c = 0; c < kLtNT; c++) thk[c] = f4{0.f, 0.f, 0.f, 0.f};
-        // (B1) node 0: w = x_0 + tau p'_1, wbar = M XB_0; dM += XB_0 w^T is
-        // applied once per segment from the staged (XB_0, w) pairs.  With fewer
-        // row tiles than waves, the waves past the last tile (whose product
-        // tiles are padding) form wbar, one thread per output summing its terms
-        // in order, and stage the pair while the others run (B2)'s product
-        // A XB; otherwise the eight waves first sum quarters of each row's terms.
-        float* st = stage + int64_t(k - k0) * 2 * D;
-        f4 acc[kLtNT];
-        if constexpr (kIdleWaves > 0) {
-          if (L.has) {
-            gemm_nodes<D>(af, XB, L, R, acc);  // (A XB)_j
-          } else {
+              for (int ri = 0; ri < RPW; ri++)
+                st4(st + D + c.coord(ri), x0[ri] + tau * c.P[ri][0]);
+        }
+      }
+      if constexpr (C::kRows) {
+        c.load_tiles(adj, c.XB);
+        c.load_tiles(adj + TF, c.ZB);
+      }
+      float touched = 0.f;
+      typename C::Tiles pk;
+      if constexpr (C::kRows) c.load_tiles(seg + int64_t(nk - 1) * 2 * TF + TF, pk);
+      for (int k = nk - 1; k >= 0; k--) {
+        float* cur = seg + int64_t(k) * 2 * TF;
+        c.step(a, eps, stage + int64_t(k) * 2 * D, cur, k > 0 ? cur - 2 * TF : nullptr, pk, touched, xb0, zb0, s1, s2);
+      }
+      // dM += sum over the segment's steps of XB_0 w^T, in FP32 from the kept pairs
+      if constexpr (S::kReg) {
+        __threadfence_block();
+        for (int j0 = 0; j0 < nk; j0 += 4) {
+          float u[RPW], v[RPW];
+          const bool ok = j0 + lk < nk;
+          const float* st = stage + int64_t(ok ? j0 + lk : 0) * 2 * D;
 #pragma unroll
-            for (int c = 0; c < kLtNT; c++) acc[c] = f4{0.f, 0.f, 0.f, 0.f};
-            // the terms' loads are issued W at a time ahead of their products;
-            // the opaque column keeps M's loads inside the step
-            constexpr int W = D % 25 == 0 ? 25 : (D % 16 == 0 ? 16 : (D % 8 == 0 ? 8 : 4));
-            for (int i = L.tid - 64 * L.RT; i < D; i += 64 * kIdleWaves) {
-              int col = i;
-              asm volatile("" : "+v"(col));
-              float part = 0.f;
-              for (int s0 = 0; s0 < D; s0 += W) {
-                float mv[W], xv[W];
+          for (int ri = 0; ri < RPW; ri++) {
+            u[ri] = ok ? st[16 * ri + lr] : 0.f;
+            v[ri] = ok ? st[D + 16 * ri + lr] : 0.f;
+          }
 #pragma unroll
-                for (int h = 0; h < W; h++) {
-                  mv[h] = a.M[(s0 + h) * D + col];
-                  xv[h] = XB[s0 + h];
-                }
-                __builtin_amdgcn_sched_barrier(0);
+          for (int ri = 0; ri < RPW; ri++)
 #pragma unroll
-                for (int h = 0; h < W; h++) part += mv[h] * xv[h];
-              }
-              s_wb[i] = part;
-              st[i] = XB[i];
-              st[D + i] = S0[i] + tau * S1[LD + i];
-            }
+            for (int ct = 0; ct < RT; ct++) c.dM[ri][ct] = mfma4(u[ri], v[ct], c.dM[ri][ct]);
+        }
+      } else {
+        constexpr int R = 32;  // steps per pass: two [R][d + 1] arrays fit the smallest images
+        static_assert(2 * R * LD <= 3 * S::kImg, "staging fits the images");
+        float *S0 = smem, *S1 = smem + R * LD;
+        for (int r0 = 0; r0 < nk; r0 += R) {
+          const int nr = min(R, nk - r0);
+          __syncthreads();
+          for (int e = tid; e < R * LD; e += S::kThreads) {
+            const int j = e / LD, i = e - j * LD;
+            const bool ok = j < nr && i < D;
+            const float* st = stage + int64_t(r0 + j) * 2 * D;
+            S0[e] = ok ? st[i] : 0.f;
+            S1[e] = ok ? st[D + i] : 0.f;
           }
           __syncthreads();
-        } else {
-          const int i = L.tid & 127, g = L.tid >> 7;
-          if (i < D) {
-            constexpr int KQ = (D + 3) / 4;
-            // W terms per trip, their loads issued together ahead of the
-            // products (g < 4, so with d a multiple of 4 every term exists and
-            // no branch guards a load); the opaque column keeps M's loads
-            // inside the step
-            constexpr int W = KQ % 5 == 0 ? 5 : (KQ % 4 == 0 ? 4 : 1);
-            int col = i;
-            asm volatile("" : "+v"(col));
-            float part = 0.f;
-            for (int s0 = 0; s0 < KQ; s0 += W) {
-              float mv[W], xv[W];
+          if constexpr (C::kRows) {
+            const int row = 16 * c.wave + lr, rc = row < D ? row : D;
+            f4 acc[RT];
 #pragma unroll
-              for (int h = 0; h < W; h++) {
-                const int kq = g * KQ + s0 + h;
-                const bool ok = 4 * KQ == D || kq < D;
-                mv[h] = ok ? a.M[kq * D + col] : 0.f;
-                xv[h] = ok ? XB[kq] : 0.f;
+            for (int ct = 0; ct < RT; ct++) acc[ct] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int j = lk; j < R; j += 4) {
+              const float u = S0[j * LD + rc];
+#pragma unroll
+              for (int ct = 0; ct < RT; ct++) {
+                const int col = 16 * ct + lr;
+                acc[ct] = mfma4(u, S1[j * LD + (col < D ? col : D)], acc[ct]);
               }
-              __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-              for (int h = 0; h < W; h++) part += mv[h] * xv[h];
             }
-            s_wb[g * 128 + i] = part;
+            float* pm = part + DD + int64_t(16 * c.wave + 4 * lk) * D + lr;
+#pragma unroll
+            for (int ct = 0; ct < RT; ct++)
+#pragma unroll
+              for (int r = 0; r < 4; r++)
+                if (16 * c.wave + 4 * lk + r < D && 16 * ct + lr < D) pm[r * D + 16 * ct] += acc[ct][r];
           }
-          if (L.tid < D) {
-            st[L.tid] = XB[L.tid];
-            st[D + L.tid] = S0[L.tid] + tau * S1[LD + L.tid];
-          }
-          __syncthreads();
-          gemm_nodes<D>(af, XB, L, R, acc);  // (A XB)_j
         }
-        if (L.tid < D) ZB[L.tid] += wbar(L.tid);
-        // (B2) primal step transposed
-        {
-#pragma unroll
-          for (int c = 0; c < kLtNT; c++) {
-            if (c >= NT) continue;
-            const int j = 16 * c + L.lr + 1;
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-              const bool ok = L.iok[r] && j <= Np;
-              const bool prim = j <= Np - 1;
-              const int e = lo + 16 * c * LD + L.ic[r];
-              const float xb = prim ? XB[e] : 0.f;
-              const float xbm = (j >= 2) ? XB[e - LD] : 0.f;
-              const float pp = S1[e], xk = S0[e];
-              const float th = tanh_fast(xk), om = 1.f - th * th;
-              thk[c][r] = th;
-              // x_N is fixed: no primal step and no (A XB)_N term at j = N
-              float pbd = -tau * xb - (prim ? td * acc[c][r] : 0.f) - td * eps * om * xb + tau * xbm;
-              if (j == 1) pbd += tau * wbar(L.ic[r] < D ? L.ic[r] : 0);
-              // entries that do not move are written back unchanged (no branch)
-              const float pbo = PB[e], zbo = ZB[e];
-              PB[e] = ok ? (pbo + pbd) * c1 : pbo;  // with (C1) vbar = c1 PB folded in
-              ZB[e] = ok ? zbo + (xb + 2.f * td * eps * om * th * pp * xb) : zbo;
-              deps += (ok && prim) ? -td * om * pp * xb : 0.f;
-            }
-          }
-          gemm_outer<D>(L, S1, XB, -td, 1, Np - 1, dA);
-        }
-        __syncthreads();
-        // (C1) vbar = c1 PB: applied above where (B2) writes PB (every entry
-        // of nodes 1..N is written there once; node 0's row and the padding
-        // column stay 0)
-        // (C2) dual step transposed; Zpre into the XB array
-        {
-          f4 acc[kLtNT];
-          gemm_nodes<D>(atf, PB, L, R, acc);  // (A^T vbar)_j
-#pragma unroll
-          for (int c = 0; c < kLtNT; c++) {
-            if (c >= NT) continue;
-            const int j = 16 * c + L.lr + 1;
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-              const bool ok = L.iok[r] && j <= Np;
-              const int e = lo + 16 * c * LD + L.ic[r];
-              const float vb = PB[e], vbn = (j < Np) ? PB[e + LD] : 0.f;
-              const float th = thk[c][r];
-              // entries past N and in the padding column hold zero in every array
-              const float zbo = ZB[e];
-              ZB[e] = ok ? zbo + (lam * acc[c][r] + lam * eps * (1.f - th * th) * vb) : zbo;
-              XB[e] = ok ? sigma * (vb - vbn) : 0.f;
-              deps += ok ? lam * th * vb : 0.f;
-            }
-          }
-          if (L.tid < D) XB[L.tid] = -sigma * PB[LD + L.tid];
-          if (k > k0) lt_rows_load<D>(segx + int64_t(k - 1 - k0) * 2 * RL, RL, Np, rows);
-          gemm_outer<D>(L, PB, S0, lam, 1, Np, dA);
-        }
-        __syncthreads();
-        // (D) roles: x-adjoint <- Xpre (ZB array), z-adjoint <- Zpre (XB array)
-        float* tmp = XB;
-        XB = ZB;
-        ZB = tmp;
-      }
-      // dM += sum over the segment's steps of XB_0 w^T: one matrix-core outer
-      // product over the staged rows (S0, S1 are free until the next segment)
-      __syncthreads();
-      for (int r0 = 0; r0 < k1 - k0; r0 += R) {
-        const int nr = min(R, k1 - k0 - r0);
-        for (int e = L.tid; e < R * LD; e += kLtThreads) {
-          const int j = e / LD, i = e - j * LD;
-          const bool ok = j < nr && i < D;
-          const float* st = stage + int64_t(r0 + j) * 2 * D;
-          S0[e] = ok ? st[i] : 0.f;
-          S1[e] = ok ? st[D + i] : 0.f;
-        }
-        __syncthreads();
-        int rb = 16 * L.wave + 4 * L.lk;
-        asm volatile("" : "+v"(rb));
-        float* pm = part + DD + int64_t(rb) * D + L.lr;
-        f4 dMf[CT];
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = rb + r, col = 16 * ct + L.lr;
-            dMf[ct][r] = (L.has && row < D && col < D) ? pm[r * D + 16 * ct] : 0.f;
-          }
-        gemm_outer<D>(L, S0, S1, 1.f, 0, nr - 1, dMf);
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = rb + r, col = 16 * ct + L.lr;
-            if (L.has && row < D && col < D) pm[r * D + 16 * ct] = dMf[ct][r];
-          }
         __syncthreads();
       }
     }
+    c.deps += c.lam * s2 - tau * c.delta * s1;
     // d phi / d x: every x_j^0 = x + noise (j < N), x_N = x, z^0 = x^0
-    if (L.tid < D) {
-      float g = 0.f;
-      for (int j = 0; j <= Np; j++) g += XB[j * LD + L.tid] + ZB[j * LD + L.tid];
-      b.dphi_dx[pt * D + L.tid] = g;
-    }
+    if constexpr (C::kRows)
+#pragma unroll
+      for (int ri = 0; ri < RPW; ri++) {
+        f4 g;
+        if constexpr (S::kReg) g = xb0[ri] + zb0[ri];
+        else g = c.first_col(ld4(c.sXb0 + (c.rows_ok(0) ? c.coord(0) : 0)) +
+                             ld4(c.sZb0 + (c.rows_ok(0) ? c.coord(0) : 0)));
+#pragma unroll
+        for (int t = 0; t < NT; t++) g += c.XB[ri][t] + c.ZB[ri][t];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const float v = group_sum<16>(g[r]);
+          if (lr == 0 && c.rows_ok(ri)) b.dphi_dx[pt * D + c.coord(ri) + r] = v;
+        }
+      }
     __syncthreads();
   }
-  // ---- per-workgroup partial parameter gradients (dM, dQ are already there) ----------------
+  // ---- per-workgroup partial parameter gradients ----------------------------------------
+  if constexpr (C::kRows)
 #pragma unroll
-  for (int ct = 0; ct < CT; ct++)
+    for (int ri = 0; ri < RPW; ri++)
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int row = 16 * L.wave + 4 * L.lk + r, col = 16 * ct + L.lr;
-      if (L.has && row < D && col < D) part[row * D + col] = dA[ct][r];
-    }
-  deps = wg_sum(deps, s_red);
-  if (L.tid == 0) part[3 * DD] = deps;
+      for (int ct = 0; ct < RT; ct++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int row = c.coord(ri) + r, col = 16 * ct + lr;
+          if (row < D && col < D) {
+            part[row * D + col] = c.dA[ri][ct][r];
+            if constexpr (S::kReg) part[DD + row * D + col] = c.dM[ri][ct][r];
+          }
+        }
+  float zero = 0.f;
+  c.sum2(c.deps, zero);
+  if (tid == 0) part[3 * DD] = c.deps;
 }
 
-// Sum the per-workgroup partials (fixed order: deterministic).
-__global__ void k_lt_reduce_parts(const float* part, int nwg, int d, float* out /* [3 d^2 + 1] */) {
+template <int D, int NT>
+__global__ void __launch_bounds__((LtShape<D, NT>::kThreads), 2) k_lt_backward(LtBwdArgs b) {
+  using S = LtShape<D, NT, true>;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (S::kAux && wave == S::RT) lt_backward_wave<D, NT, S::kAux ? kAuxWave : kRowWave>(b, smem);
+  else if (S::kTail && wave == S::RT - 1) lt_backward_wave<D, NT, S::kTail ? kTailWave : kRowWave>(b, smem);
+  else lt_backward_wave<D, NT, kRowWave>(b, smem);
+}
+
+// Sum the per-workgroup partials (fixed order: deterministic).  A block takes
+// 64 entries; its 16 waves sum every 16th partial each, all loads independent,
+// and the sums meet in LDS.  Bound by memory latency: one thread per entry over
+// all partials in turn took 99 us for 256 partials of d = 100 (184 us for 777
+// of d = 32); this takes 9.5 us (5.4 us).
+constexpr int kRedWaves = 16;
+__global__ void __launch_bounds__(64 * kRedWaves) k_lt_reduce_parts(const float* part, int nwg, int d,
+                                                                    float* out /* [3 d^2 + 1] */) {
+  __shared__ float s[kRedWaves][64];
   const int64_t DD = int64_t(d) * d, W = 3 * DD + 1;
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= W) return;
-  float s = 0.f;
-  for (int g = 0; g < nwg; g++) s += part[g * W + e];
-  out[e] = s;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t e = int64_t(blockIdx.x) * 64 + lane;
+  float v = 0.f;
+  if (e < W)
+#pragma unroll 16
+    for (int g = wave; g < nwg; g += kRedWaves) v += part[g * W + e];
+  s[wave][lane] = v;
+  __syncthreads();
+  if (wave == 0 && e < W) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < kRedWaves; w++) t += s[w][lane];
+    out[e] = t;
+  }
 }
 
-// C = scale A B (row-major d x d)
-__global__ void k_lt_matmul(const float* Aa, const float* Bb, int d, float* C, float scale) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= d * d) return;
-  const int r = e / d, c = e - r * d;
-  float s = 0.f;
-  for (int k = 0; k < d; k++) s += Aa[r * d + k] * Bb[k * d + c];
-  C[e] = scale * s;
+// Row blockIdx.x of S = scale M dM M: u = M[row] dM, then u M; four groups of
+// threads take a quarter of the terms each.  (Two launches of a thread per
+// entry took 26 us each at d = 100; this takes 5 us.)
+__global__ void __launch_bounds__(4 * kLtMaxD) k_lt_mdm(const float* M, const float* dM, int d, float scale, float* S) {
+  __shared__ float s_u[kLtMaxD], s_part[4][kLtMaxD];
+  const int c = threadIdx.x % kLtMaxD, g = threadIdx.x / kLtMaxD, q = d / 4;
+  auto vec_mat = [&](const float* B, auto u) {
+    float v = 0.f;
+    if (c < d)
+#pragma unroll 8
+      for (int k = g * q; k < (g + 1) * q; k++) v += u(k) * B[k * d + c];
+    s_part[g][c] = v;
+    __syncthreads();
+    return (s_part[0][c] + s_part[1][c]) + (s_part[2][c] + s_part[3][c]);
+  };
+  const float u = vec_mat(dM, [&](int k) { return M[blockIdx.x * d + k]; });
+  if (g == 0) s_u[c] = u;
+  __syncthreads();
+  const float v = vec_mat(M, [&](int k) { return s_u[k]; });
+  if (g == 0 && c < d) S[blockIdx.x * d + c] = scale * v;
 }
 
 // dh = [deps, dA]; dg = dQ_direct + sym(S) with S = -tau M dM M.
@@ -965,6 +507,8 @@ __global__ void k_lt_grad_out(const float* sums, const float* S, int d, float* d
   dg[e] = sums[2 * DD + e] + 0.5f * (S[r * d + c] + S[c * d + r]);
 }
 
+// Set-up of a call: block 0 inverts, the others pack A's operands.
+//
 // (I + tau Q_s)^{-1} by Gauss-Jordan exchange steps with row pivoting in double
 // precision, one workgroup, the matrix in registers: thread (tr, tc) holds rows
 // tr + TR u and columns tc + 16 m.  Also clears the solve's counters.
@@ -984,12 +528,27 @@ struct LtInv {
 };
 
 template <int D>
-__global__ void __launch_bounds__(LtInv<D>::kThreads) k_lt_inverse(const float* Q, double tau, float* Mout,
-                                                                   int32_t* counters) {
+__global__ void __launch_bounds__(LtInv<D>::kThreads) k_lt_setup(const float* Q, const float* hp, double tau, float* Mout,
+                                                                 float* Mc, float* Qs, float* packed,
+                                                                 int32_t* counters) {
   constexpr int TR = LtInv<D>::TR, RU = LtInv<D>::RU, CM = LtInv<D>::CM;
   __shared__ double s_col[2][D], s_row[2][16 * CM];  // alternate between steps: one barrier each way is enough
   __shared__ int s_piv[D];
   const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15, lane = tid & 63;
+  using Frag = LtFrag<D>;
+  if (blockIdx.x > 0) {  // A and A^T as operands, rows past d zero
+    constexpr int kRows = LtShape<D, 1>::RT * 16, kPairs = D / 2;
+    const float* A = hp + 1;
+    for (int e = (blockIdx.x - 1) * LtInv<D>::kThreads + tid; e < 2 * kRows * kPairs;
+         e += (gridDim.x - 1) * LtInv<D>::kThreads) {
+      const int matrix = e / (kRows * kPairs), row = e / kPairs % kRows, k = 2 * (e % kPairs);
+      const int rs = matrix ? 1 : D, ks = matrix ? D : 1;
+      const float u = row < D ? A[row * rs + k * ks] : 0.f, v = row < D ? A[row * rs + (k + 1) * ks] : 0.f;
+      Frag::pack(packed, matrix, row, k, u, v);
+      if constexpr (LtShape<D, 1>::kReg) Frag::pack(packed, matrix, row, k + 1, v, v);
+    }
+    return;
+  }
   if (tid < kLtCounters) counters[tid] = 0;
   double T[RU][CM];
 #pragma unroll
@@ -1072,7 +631,13 @@ __global__ void __launch_bounds__(LtInv<D>::kThreads) k_lt_inverse(const float* 
 #pragma unroll
     for (int m = 0; m < CM; m++) {
       const int r = tr + TR * u, c = tc + 16 * m;
-      if (r < D && c < D) Mout[s_var[r] * D + s_piv[c]] = float(T[u][m]);
+      if (r < D && c < D) {
+        const int i = s_var[r], j = s_piv[c];
+        Mout[i * D + j] = float(T[u][m]);
+        Mc[(j / 4 * D + i) * 4 + j % 4] = float(T[u][m]);
+        Qs[r * D + c] = 0.5f * (Q[r * D + c] + Q[c * D + r]);
+        if constexpr (LtShape<D, 1>::kReg) Frag::pack(packed, 2, i, j, float(T[u][m]), 0.f);
+      }
     }
 }
 
@@ -1083,7 +648,7 @@ __global__ void __launch_bounds__(LtInv<D>::kThreads) k_lt_inverse(const float* 
 struct LtState {
   int d = 0;
   int n_cu = 0;
-  float* M = nullptr;           // d*d
+  float* M = nullptr;           // M, M in chunks of four columns, Q_s (d*d each), packed operands
   int32_t* counters = nullptr;  // [0] forward head, [1] inverse failure
   int32_t* scratch_i = nullptr; // iterations and statuses of the forward pass in value_grad
   size_t scratch_bytes = 0;
@@ -1094,12 +659,16 @@ struct LtState {
   float* part = nullptr;
   size_t part_bytes = 0;
   float* sums = nullptr;  // 3 d^2 + 1
-  float* tmp = nullptr;   // 2 d^2
+  float* tmp = nullptr;   // d^2
 };
 
 typedef const void* KernelPtr;
 
-// Forward kernel for (d, N_max): its column tiles cover N_max.
+// Floats of the largest packed copy (d = 128: two matrices; d = 32: three).
+constexpr size_t kLtPacked = 2 * LtFrag<128>::kMatrix;
+static_assert(kLtPacked >= 3 * size_t(LtFrag<32>::kMatrix) && kLtPacked >= 2 * size_t(LtFrag<100>::kMatrix), "packed operands fit");
+
+// A kernel for (d, N_max): its column tiles cover N_max.
 struct LtKernel {
   KernelPtr fn = nullptr;
   int threads = 0;
@@ -1107,37 +676,32 @@ struct LtKernel {
 };
 
 template <int D, int NT>
-static LtKernel forward_of() {
+static LtKernel kernel_of(bool back) {
+  if (back)
+    return {reinterpret_cast<KernelPtr>(&k_lt_backward<D, NT>), LtShape<D, NT>::kThreads,
+            sizeof(float) * LtShape<D, NT, true>::kLdsFloats};
   return {reinterpret_cast<KernelPtr>(&k_lt_forward<D, NT>), LtShape<D, NT>::kThreads,
           sizeof(float) * LtShape<D, NT>::kLdsFloats};
 }
 template <int D>
-static LtKernel forward_tiles(int N_max) {
+static LtKernel kernel_tiles(int N_max, bool back) {
   switch ((N_max + 15) / 16) {
-    case 1: return forward_of<D, 1>();
-    case 2: return forward_of<D, 2>();
-    case 3: return forward_of<D, 3>();
-    default: return forward_of<D, 4>();
-  }
-}
-static LtKernel forward_kernel(int d, int N_max) {
-  switch (d) {
-    case 16: return forward_tiles<16>(N_max);
-    case 32: return forward_tiles<32>(N_max);
-    case 100: return forward_tiles<100>(N_max);
-    case 128: return forward_tiles<128>(N_max);
+    case 1: return kernel_of<D, 1>(back);
+    case 2: return kernel_of<D, 2>(back);
+    case 3: return kernel_of<D, 3>(back);
+    case 4:
+      if constexpr (D < 128) return kernel_of<D, 4>(back);  // d = 128 is built for N_max <= 48
   }
   return {};
 }
-
-static KernelPtr backward_kernel(int d) {
+static LtKernel lt_kernel(int d, int N_max, bool back) {
   switch (d) {
-    case 16: return reinterpret_cast<KernelPtr>(&k_lt_backward<16>);
-    case 32: return reinterpret_cast<KernelPtr>(&k_lt_backward<32>);
-    case 100: return reinterpret_cast<KernelPtr>(&k_lt_backward<100>);
-    case 128: return reinterpret_cast<KernelPtr>(&k_lt_backward<128>);
+    case 16: return kernel_tiles<16>(N_max, back);
+    case 32: return kernel_tiles<32>(N_max, back);
+    case 100: return kernel_tiles<100>(N_max, back);
+    case 128: return kernel_tiles<128>(N_max, back);
   }
-  return nullptr;
+  return {};
 }
 
 #define LT_HIP(expr, what)                                                                                    \
@@ -1148,9 +712,10 @@ static KernelPtr backward_kernel(int d) {
 
 int lt_create(LtState** out, const hjpd_desc& desc) {
   *out = nullptr;
-  const LtKernel fwd = forward_kernel(desc.d, desc.N_max);
-  if (!fwd.fn) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for d in {16,32,100,128}");
+  if (!lt_kernel(desc.d, 1, false).fn) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for d in {16,32,100,128}");
   if (desc.N_max > kLtMaxN) return hjpd_fail(HJPD_EUNSUPPORTED, "LINEAR_TANH is built for N_max <= 64");
+  const LtKernel fwd = lt_kernel(desc.d, desc.N_max, false), bwd = lt_kernel(desc.d, desc.N_max, true);
+  if (!fwd.fn) return hjpd_fail(HJPD_EDEVICE, "cannot reserve LDS for the linear-tanh kernels (d = 128: N_max <= 48)");
   LtState* s = new LtState();
   s->d = desc.d;
   int dev = 0;
@@ -1161,16 +726,15 @@ int lt_create(LtState** out, const hjpd_desc& desc) {
   }
   s->n_cu = prop.multiProcessorCount;
   if (hipFuncSetAttribute(fwd.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(fwd.lds)) != hipSuccess ||
-      hipFuncSetAttribute(backward_kernel(desc.d), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          int(lt_lds_backward(desc.d, desc.N_max))) != hipSuccess) {
+      hipFuncSetAttribute(bwd.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bwd.lds)) != hipSuccess) {
     delete s;
     return hjpd_fail(HJPD_EDEVICE, "cannot reserve LDS for the linear-tanh kernels");
   }
   const size_t dd = size_t(desc.d) * desc.d;
-  if (hipMalloc(&s->M, sizeof(float) * dd) != hipSuccess ||
+  if (hipMalloc(&s->M, sizeof(float) * (3 * dd + kLtPacked))  != hipSuccess ||
       hipMalloc(&s->counters, sizeof(int32_t) * kLtCounters) != hipSuccess ||
       hipMalloc(&s->sums, sizeof(float) * (3 * dd + 1)) != hipSuccess ||
-      hipMalloc(&s->tmp, sizeof(float) * 2 * dd) != hipSuccess) {
+      hipMalloc(&s->tmp, sizeof(float) * dd) != hipSuccess) {
     lt_destroy(s);
     return hjpd_fail(HJPD_ENOMEM, "linear-tanh workspace");
   }
@@ -1207,6 +771,9 @@ static void fill_args(LtArgs& a, LtState* st, const hjpd_desc& d, int64_t n, con
   a.hp = (const float*)hp;
   a.Q = (const float*)gp;
   a.M = st->M;
+  a.Mc = st->M + size_t(d.d) * d.d;
+  a.Qs = st->M + 2 * size_t(d.d) * d.d;
+  a.packed = st->M + 3 * size_t(d.d) * d.d;
   a.phi = (float*)phi;
   a.xtraj = (float*)xtraj;
   a.ptraj = (float*)ptraj;
@@ -1225,15 +792,17 @@ static void fill_args(LtArgs& a, LtState* st, const hjpd_desc& d, int64_t n, con
   a.ckpt_every = 1;
 }
 
-static int lt_setup(LtState* st, const hjpd_desc& d, const void* gp, hipStream_t s) {
+static int lt_setup(LtState* st, const hjpd_desc& d, const void* hp, const void* gp, hipStream_t s) {
+  const size_t dd = size_t(d.d) * d.d;
   auto launch = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), 0, s, (const float*)gp, d.tau, st->M, st->counters);
+    hipLaunchKernelGGL(kern, dim3(1 + kLtPackBlocks), dim3(threads), 0, s, (const float*)gp, (const float*)hp, d.tau,
+                       st->M, st->M + dd, st->M + 2 * dd, st->M + 3 * dd, st->counters);
   };
   switch (d.d) {
-    case 16: launch(k_lt_inverse<16>, LtInv<16>::kThreads); break;
-    case 32: launch(k_lt_inverse<32>, LtInv<32>::kThreads); break;
-    case 100: launch(k_lt_inverse<100>, LtInv<100>::kThreads); break;
-    default: launch(k_lt_inverse<128>, LtInv<128>::kThreads); break;
+    case 16: launch(k_lt_setup<16>, LtInv<16>::kThreads); break;
+    case 32: launch(k_lt_setup<32>, LtInv<32>::kThreads); break;
+    case 100: launch(k_lt_setup<100>, LtInv<100>::kThreads); break;
+    default: launch(k_lt_setup<128>, LtInv<128>::kThreads); break;
   }
   LT_HIP(hipGetLastError(), "linear-tanh set-up kernel");
   return HJPD_OK;
@@ -1242,12 +811,12 @@ static int lt_setup(LtState* st, const hjpd_desc& d, const void* gp, hipStream_t
 int lt_solve(LtState* st, const hjpd_desc& d, int64_t n, const void* x, const void* t, const int32_t* N,
              const void* hp, const void* gp, void* phi, void* xtraj, void* ptraj, int32_t* iters, int32_t* status,
              hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, int* launches, bool* timing_valid) {
-  int rc = lt_setup(st, d, gp, s);
+  int rc = lt_setup(st, d, hp, gp, s);
   if (rc) return rc;
   LtArgs a;
   fill_args(a, st, d, n, x, t, N, hp, gp, phi, xtraj, ptraj, iters, status, d.max_iter,
             (d.flags & HJPD_FIXED_ITERS) != 0);
-  const LtKernel k = forward_kernel(d.d, d.N_max);
+  const LtKernel k = lt_kernel(d.d, d.N_max, false);
   void* args[] = {&a};
   if (ev0) LT_HIP(hipEventRecord(ev0, s), "hipEventRecord");
   LT_HIP(hipLaunchKernel(k.fn, dim3(lt_grid(st, k.fn, k.threads, k.lds, n)), dim3(k.threads), args, k.lds, s),
@@ -1258,8 +827,11 @@ int lt_solve(LtState* st, const hjpd_desc& d, int64_t n, const void* x, const vo
   return HJPD_OK;
 }
 
-static int grow(void** p, size_t* cap, size_t need) {
+// Buffers grow on demand and are kept; earlier work on the context may still
+// use one that is replaced, so the stream is finished first.
+static int grow(void** p, size_t* cap, size_t need, hipStream_t s) {
   if (need <= *cap) return HJPD_OK;
+  LT_HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
   if (*p) (void)hipFree(*p);
   *p = nullptr;
   *cap = 0;
@@ -1277,27 +849,28 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
   const int n_ckpt = (K + E - 1) / E;
   const size_t CK = size_t(d.N_max + 1) * d.d;
   const size_t dd = size_t(d.d) * d.d;
-  // buffers may be reallocated: finish earlier work on this context first
-  LT_HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
-  int rc = grow((void**)&st->ckpt, &st->ckpt_bytes, sizeof(float) * size_t(n) * (n_ckpt + 1) * 3 * CK);
+  int rc = grow((void**)&st->ckpt, &st->ckpt_bytes, sizeof(float) * size_t(n) * (n_ckpt + 1) * 3 * CK, s);
   if (rc) return rc;
-  KernelPtr kb = backward_kernel(d.d);
-  const size_t lds_b = lt_lds_backward(d.d, d.N_max);
-  const int grid_b = lt_grid(st, kb, kLtThreads, lds_b, n);
-  rc = grow((void**)&st->seg, &st->seg_bytes, sizeof(float) * size_t(grid_b) * lt_seg_floats(d.d, d.N_max, E));
+  const LtKernel kb = lt_kernel(d.d, d.N_max, true);
+  const size_t seg_wg = sizeof(float) * size_t(lt_seg_floats(d.d, d.N_max, E));
+  // several small workgroups share a CU; with long segments their buffers are
+  // held to 4 GiB together, down to one workgroup a CU
+  const int64_t fit = std::max<int64_t>(st->n_cu, int64_t((size_t(4) << 30) / seg_wg));
+  const int grid_b = int(std::min<int64_t>(lt_grid(st, kb.fn, kb.threads, kb.lds, n), fit));
+  rc = grow((void**)&st->seg, &st->seg_bytes, seg_wg * size_t(grid_b), s);
   if (rc) return rc;
-  rc = grow((void**)&st->part, &st->part_bytes, sizeof(float) * size_t(grid_b) * (3 * dd + 1));
+  rc = grow((void**)&st->part, &st->part_bytes, sizeof(float) * size_t(grid_b) * (3 * dd + 1), s);
   if (rc) return rc;
-  rc = grow((void**)&st->scratch_i, &st->scratch_bytes, sizeof(int32_t) * 2 * size_t(n));
+  rc = grow((void**)&st->scratch_i, &st->scratch_bytes, sizeof(int32_t) * 2 * size_t(n), s);
   if (rc) return rc;
-  rc = lt_setup(st, d, gp, s);
+  rc = lt_setup(st, d, hp, gp, s);
   if (rc) return rc;
   LtArgs a;
   fill_args(a, st, d, n, x, t, N, hp, gp, phi, nullptr, nullptr, st->scratch_i, st->scratch_i + n, K, true);
   a.ckpt = st->ckpt;
   a.ckpt_every = E;
   a.n_ckpt = n_ckpt;
-  const LtKernel kf = forward_kernel(d.d, d.N_max);
+  const LtKernel kf = lt_kernel(d.d, d.N_max, false);
   void* fargs[] = {&a};
   LT_HIP(hipLaunchKernel(kf.fn, dim3(lt_grid(st, kf.fn, kf.threads, kf.lds, n)), dim3(kf.threads), fargs, kf.lds, s),
          "linear-tanh forward");
@@ -1311,15 +884,14 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
   b.K = K;
   void* bargs[] = {&b};
   if (ev0) LT_HIP(hipEventRecord(ev0, s), "hipEventRecord");
-  LT_HIP(hipLaunchKernel(kb, dim3(grid_b), dim3(kLtThreads), bargs, lds_b, s), "linear-tanh backward");
+  LT_HIP(hipLaunchKernel(kb.fn, dim3(grid_b), dim3(kb.threads), bargs, kb.lds, s), "linear-tanh backward");
   if (ev1) LT_HIP(hipEventRecord(ev1, s), "hipEventRecord");
   const int W = int(3 * dd + 1);
-  hipLaunchKernelGGL(k_lt_reduce_parts, dim3((W + 255) / 256), dim3(256), 0, s, st->part, grid_b, d.d, st->sums);
-  // S = -tau M (dM M)
-  const int nb = int((dd + 255) / 256);
-  hipLaunchKernelGGL(k_lt_matmul, dim3(nb), dim3(256), 0, s, st->sums + dd, st->M, d.d, st->tmp, 1.f);
-  hipLaunchKernelGGL(k_lt_matmul, dim3(nb), dim3(256), 0, s, st->M, st->tmp, d.d, st->tmp + dd, -float(d.tau));
-  hipLaunchKernelGGL(k_lt_grad_out, dim3(nb), dim3(256), 0, s, st->sums, st->tmp + dd, d.d, (float*)dh, (float*)dg);
+  hipLaunchKernelGGL(k_lt_reduce_parts, dim3((W + 63) / 64), dim3(64 * kRedWaves), 0, s, st->part, grid_b, d.d, st->sums);
+  // S = -tau M dM M
+  hipLaunchKernelGGL(k_lt_mdm, dim3(d.d), dim3(4 * kLtMaxD), 0, s, st->M, st->sums + dd, d.d, -float(d.tau), st->tmp);
+  hipLaunchKernelGGL(k_lt_grad_out, dim3(int((dd + 255) / 256)), dim3(256), 0, s, st->sums, st->tmp, d.d, (float*)dh,
+                     (float*)dg);
   LT_HIP(hipGetLastError(), "linear-tanh gradient kernels");
   if (ev0 && ev1) {
     if (launches) *launches = 1;

@@ -54,6 +54,52 @@ typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
+// LDS pointers keep their address space, so that an address is one register
+// and a constant part of it an instruction's offset.
+typedef __attribute__((address_space(3))) float lds_f;
+typedef __attribute__((address_space(3))) f4 lds_f4;
+typedef __attribute__((address_space(3))) u2 lds_u2;
+typedef __attribute__((address_space(3))) bf8 lds_bf8;
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
+// Global pointers that pass through an opaque step (and would come out generic).
+typedef const __attribute__((address_space(1))) float glb_f;
+typedef const __attribute__((address_space(1))) f4 glb_f4;
+typedef const __attribute__((address_space(1))) bf8 glb_bf8;
+__device__ __forceinline__ f4 ld4(glb_f* p) { return *(glb_f4*)p; }
+// A pointer that is the same in every lane, kept in scalar registers.
+template <class T>
+__device__ __forceinline__ T* scalar(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  uint64_t u = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32)))) << 32) |
+               uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v)));
+  asm volatile("" : "+s"(u));
+  return reinterpret_cast<T*>(u);
+}
+__device__ __forceinline__ f4 ld4(const float* p) { return *reinterpret_cast<const f4*>(p); }
+__device__ __forceinline__ f4 ld4(const lds_f* p) { return *(const lds_f4*)p; }
+__device__ __forceinline__ void st4(float* p, f4 v) { *reinterpret_cast<f4*>(p) = v; }
+__device__ __forceinline__ void st4(lds_f* p, f4 v) { *(lds_f4*)p = v; }
+
+// The lane's number, formed anew where it is used.
+__device__ __forceinline__ uint32_t lane_now() {
+  uint32_t v;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(v));
+  return v;
+}
+
+// base + off as an LDS address that the compiler neither sees through nor
+// keeps from one loop to the next: otherwise it holds a register (and soon a
+// spill slot) for every constant offset in a loop.
+// Only the reverse sweep needs that (the forward kernel's registers suffice,
+// and it is 8 % slower with the extra instructions).
+template <bool kOpaque, class P>
+__device__ __forceinline__ P* at(P* base, uint32_t off) {
+  if constexpr (kOpaque) asm volatile("" : "+v"(off));
+  P* p = base + off;
+  if constexpr (kOpaque) asm volatile("" : "+v"(p));
+  return p;
+}
+
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -96,6 +142,9 @@ struct LtArgs {
   const float* hp;  // [eps, A (d*d)]
   const float* Q;   // [d*d]
   const float* M;   // (I + tau Q_s)^{-1}
+  const float* Mc;  // the same as [column / 4][row][4]
+  const float* Qs;  // (Q + Q^T) / 2
+  const float* packed;  // A, A^T (and M, d <= 32) as operands, LtFrag
   float* phi;
   float* xtraj;
   float* ptraj;
@@ -113,7 +162,7 @@ struct LtArgs {
   int n_ckpt;
 };
 
-template <int D, int NT>
+template <int D, int NT, bool BACK = false>
 struct LtShape {
   static_assert(D % 4 == 0 && (D <= 32 ? D % 16 == 0 : D % 32 == 0 || D % 32 == 4), "built for d in {16, 32, 100, 128}");
   static constexpr int RT = (D + 15) / 16;
@@ -125,55 +174,90 @@ struct LtShape {
   static constexpr int KB = kReg ? 0 : D / 32;       // bfloat16 k-steps of a product
   static constexpr bool kTail = !kReg && D % 32 != 0; // one FP32 k-step of 4 after them
   static constexpr int ROWS = 16 * NT;               // image rows (columns of a product)
-  // An image piece is laid out [k / 8][row][8] (M: [k / 4][row][4]): the 16-byte
-  // reads of any 16 lanes with distinct rows, and the 8-byte writes of 32 lanes,
-  // cover the 64 banks once.  Rows padded to 16 bytes over a power of two lost
-  // 2,850 of 6,240 LDS cycles an iteration to conflicts (d = 100, N = 50).
-  static constexpr int PIECE = 32 * KB * ROWS;  // bfloat16 per piece
-  static constexpr int MR = D;                  // rows of M in LDS
-  // LDS in floats: two images (X, P), their FP32 tails, M, the node-0 vector, reduction slots
+  // An image piece is laid out [k / 8][row][8], the rows of odd chunks taken
+  // with bits 2 and 3 flipped (M: [k / 4][row][4]): the 16-byte reads and 8-byte
+  // writes of a wave then cover the 64 banks evenly, and so do the transposed
+  // reads of the reverse sweep, which take two neighbouring chunks at once.
+  // Rows padded to 16 bytes over a power of two lost 2,850 of 6,240 LDS cycles
+  // an iteration to conflicts (d = 100, N = 50).
+  static constexpr int CH = kReg ? 0 : 4 * KB + 2 * (BACK && kTail);  // chunks; the reverse sweep's outer products take the tail's row tile too
+  static constexpr int PIECE = 8 * CH * ROWS;   // bfloat16 per piece
+  static constexpr int MR = D;                  // rows of M
+  // LDS in floats.  Forward: two images (X, P), their FP32 tails, M, vectors,
+  // reduction slots.  Reverse sweep: three images (the third also holds the
+  // recompute's tanh), M stays in global memory, and the multipliers' adjoint.
   static constexpr int kImg = kReg ? 0 : 3 * PIECE / 2;
+  static constexpr int kImgs = BACK ? 3 : 2;
   static constexpr int kTailF = kTail ? 4 * ROWS : 0;
-  static constexpr int kM = kReg ? 0 : D * MR;
-  static constexpr int kVec = 16 * RT;
+  static constexpr int kM = kReg || BACK ? 0 : D * MR;
+  static constexpr int kVec = 16 * RT, kVecs = BACK ? 8 : 4;
   // tanh(x_j) from the dual step to the primal step, where it fits beside the rest
   static constexpr bool kThLds = !kReg && D < 128;
-  static constexpr int kTh = kThLds ? 256 * RT * NT : 0;
-  static constexpr int kLdsFloats = 2 * kImg + 2 * kTailF + kM + 4 * kVec + kTh + 2 * W + 2;
+  static constexpr int kTh = kThLds && !BACK ? 256 * RT * NT : 0;
+  static constexpr bool kPbLds = BACK && !kReg && D < 128;
+  static constexpr int kPb = kPbLds ? 256 * RT * NT : 0;
+  // d <= 32: rows of two operands of an outer product, row length 16 mod 64 (conflict-free columns)
+  static constexpr int LDW = D == 16 ? 16 : 48;
+  static constexpr int kScratch = BACK && kReg ? 2 * ROWS * LDW : 0;
+  static constexpr int kLdsFloats = kImgs * kImg + 2 * kTailF + kM + kVecs * kVec + kTh + kPb + kScratch + 2 * W + 2;
 };
 
-// A matrix's rows of one wave as A operands.
-template <int D, int NT>
+// A matrix's rows of one wave as A operands, read from a packed copy that the
+// set-up kernel makes (every load 1 KB a wave, shared by all workgroups and so
+// in L2): the reverse sweep holds one matrix at a time and reads it again in
+// every step, where the compiler otherwise kept both through scratch memory,
+// which is per workgroup and does not fit L2.
+template <int D>
 struct LtFrag {
-  using S = LtShape<D, NT>;
+  using S = LtShape<D, 1>;
+  static constexpr int kWave = S::kReg ? S::RPW * S::RPW * 256 : 3 * S::KB * 256 + 64;  // floats of one wave's rows
+  static constexpr int kMatrix = kWave * (S::kReg ? 1 : S::RT);
   float f[S::kReg ? S::RPW : 1][S::kReg ? 4 * S::RPW : 1];  // FP32 operands (kReg), or the tail's
   bf8 h[S::kReg ? 1 : S::KB], m[S::kReg ? 1 : S::KB], l[S::kReg ? 1 : S::KB];
 
-  // entry (row, k) at a[row * rs + k * ks]
-  __device__ void load(const float* a, int rs, int ks, int wave, int lr, int lk) {
+  // matrix: 0 = A, 1 = A^T, 2 = M (d <= 32).  The opaque address keeps the reads where they are written.
+  __device__ __forceinline__ void load(const float* packed, int matrix, int wave, int lane) {
+    glb_f* q = (glb_f*)packed + (matrix * kMatrix + wave * kWave);
+    asm volatile("" : "+s"(q));
     if constexpr (S::kReg) {
 #pragma unroll
       for (int ro = 0; ro < S::RPW; ro++)
 #pragma unroll
-        for (int q = 0; q < 4 * S::RPW; q++)
-          f[ro][q] = a[(16 * ro + lr) * rs + (16 * (q / 4) + 4 * lk + q % 4) * ks];
+        for (int e = 0; e < S::RPW; e++) {
+          const f4 v = ld4(q + (ro * S::RPW + e) * 256 + lane * 4);
+#pragma unroll
+          for (int r = 0; r < 4; r++) f[ro][4 * e + r] = v[r];
+        }
     } else {
-      const int row = 16 * wave + lr;
-      const bool ok = row < D;
 #pragma unroll
       for (int s = 0; s < S::KB; s++) {
-        uint32_t hh[4], mm[4], ll[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const int k = 32 * s + 8 * lk + 2 * e;
-          const float u = ok ? a[row * rs + k * ks] : 0.f, v = ok ? a[row * rs + (k + 1) * ks] : 0.f;
-          split_pair(u, v, hh[e], mm[e], ll[e]);
-        }
-        h[s] = __builtin_bit_cast(bf8, hh);
-        m[s] = __builtin_bit_cast(bf8, mm);
-        l[s] = __builtin_bit_cast(bf8, ll);
+        h[s] = *(glb_bf8*)(q + (3 * s + 0) * 256 + lane * 4);
+        m[s] = *(glb_bf8*)(q + (3 * s + 1) * 256 + lane * 4);
+        l[s] = *(glb_bf8*)(q + (3 * s + 2) * 256 + lane * 4);
       }
-      if constexpr (S::kTail) f[0][0] = ok ? a[row * rs + (32 * S::KB + lk) * ks] : 0.f;
+      if constexpr (S::kTail) f[0][0] = q[3 * S::KB * 256 + lane];
+    }
+  }
+  // Entry (row, k) of a matrix at its place in the packed copy (one thread per
+  // entry, k < D; with d > 32 pairs of entries: call it for even k with both).
+  __device__ static void pack(float* packed, int matrix, int row, int k, float u, float v) {
+    float* q = packed + matrix * kMatrix;
+    const int lr = row % 16;
+    if constexpr (S::kReg) {
+      q[((row / 16) * S::RPW + k / 16) * 256 + (16 * (k % 16 / 4) + lr) * 4 + k % 4] = u;
+    } else {
+      q += (row / 16) * kWave;
+      if (k < 32 * S::KB) {
+        uint32_t hml[3];
+        split_pair(u, v, hml[0], hml[1], hml[2]);
+        const int lane = 16 * (k % 32 / 8) + lr;
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+          reinterpret_cast<uint32_t*>(q)[(3 * (k / 32) + c) * 256 + lane * 4 + k % 8 / 2] = hml[c];
+      } else {
+        q[3 * S::KB * 256 + 16 * (k - 32 * S::KB) + lr] = u;
+        q[3 * S::KB * 256 + 16 * (k + 1 - 32 * S::KB) + lr] = v;
+      }
     }
   }
 };
@@ -188,23 +272,25 @@ enum : int {
 };
 
 // One point's iteration, by one wave; every wave of the workgroup runs it together.
-template <int D, int NT, int KIND>
+template <int D, int NT, int KIND, bool BACK = false>
 struct LtCore {
-  using S = LtShape<D, NT>;
-  using Frag = LtFrag<D, NT>;
+  using S = LtShape<D, NT, BACK>;
+  using Frag = LtFrag<D>;
   static constexpr int RPW = S::RPW;
   static constexpr bool kRows = KIND != kAuxWave;
   typedef f4 Tiles[RPW][NT];
 
   int tid, wave, lr, lk;
   // LDS (d > 32): bfloat16 images of X and P, their tails, M, a vector, reduction slots
-  uint16_t *imgX, *imgP;
-  float *tailX, *tailP, *sM, *sTh;
-  float *sX0, *sZ0, *sV, *sW;  // x_0, z_0, p_1 (also scratch), x_0 + tau p_1
-  float* sRed;
+  lds_u16 *imgX, *imgP, *img3;
+  lds_f *tailX, *tailP, *sTh, *sPb, *sScr;
+  std::conditional_t<BACK, glb_f*, const lds_f*> Mc;         // M in chunks of four columns, in LDS or (reverse sweep) in global memory
+  lds_f *sX0, *sZ0, *sV, *sW;  // x_0, z_0, p_1 (also scratch), x_0 + tau p_1
+  lds_f *sXb0, *sZb0, *sE, *sWb;  // reverse sweep: node 0's adjoints, XB_0 and M XB_0
+  lds_f* sRed;
   uint32_t put_at, get_at;  // this lane's element offsets into an image
   Frag fA, fAt;
-  float fM[S::kReg ? S::RPW : 1][S::kReg ? 4 * S::RPW : 1];
+  Frag fM;  // d <= 32
 
   // state of the current point
   Tiles X, P, Z;
@@ -213,49 +299,58 @@ struct LtCore {
   float delta, lam, c1;
 
   __device__ int coord(int ri) const { return 16 * (S::kReg ? ri : wave) + 4 * lk; }  // of element r = 0
+  __device__ int coord_now() const { return 16 * wave + 4 * (BACK ? int(lane_now() >> 4) : lk); }  // the same, d > 32
   __device__ int node(int t) const { return NT * lr + t + 1; }
+  __device__ int node_now() const { return NT * (BACK ? int(lane_now() & 15) : lr) + 1; }           // node(0)
   __device__ bool rows_ok(int ri) const { return S::kReg || D % 16 == 0 || coord(ri) < D; }
 
-  __device__ void setup(const LtArgs& a, float* lds) {
+  __device__ void setup(const LtArgs& a, float* shared) {
+    lds_f* lds = (lds_f*)shared;
     tid = threadIdx.x;
     wave = S::W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
     lr = tid & 15;
     lk = (tid & 63) >> 4;
-    if constexpr (kRows) {
-      fA.load(a.hp + 1, D, 1, wave, lr, lk);
-      fAt.load(a.hp + 1, 1, D, wave, lr, lk);
-    }
-    imgX = reinterpret_cast<uint16_t*>(lds);
-    imgP = reinterpret_cast<uint16_t*>(lds + S::kImg);
-    tailX = lds + 2 * S::kImg;
+    if constexpr (kRows && !BACK) load_matrices(a);
+    imgX = (lds_u16*)lds;
+    imgP = (lds_u16*)(lds + S::kImg);
+    img3 = (lds_u16*)(lds + 2 * S::kImg);
+    tailX = lds + S::kImgs * S::kImg;
     tailP = tailX + S::kTailF;
-    sM = tailP + S::kTailF;
-    sTh = sM + S::kM;
-    sX0 = sTh + S::kTh;
+    lds_f* sM = tailP + S::kTailF;
+    sTh = BACK ? lds + 2 * S::kImg : sM + S::kM;
+    sPb = sM + S::kM + S::kTh;
+    sScr = sPb + S::kPb;
+    sX0 = sScr + S::kScratch;
     sZ0 = sX0 + S::kVec;
     sV = sZ0 + S::kVec;
     sW = sV + S::kVec;
-    sRed = sW + S::kVec;
-    put_at = ((2 * wave + (lk >> 1)) * S::ROWS + lr) * 8 + (lk & 1) * 4;
-    get_at = (lk * S::ROWS + lr) * 8;
-    if constexpr (S::kReg) {
-#pragma unroll
-      for (int ro = 0; ro < RPW; ro++)
-#pragma unroll
-        for (int q = 0; q < 4 * RPW; q++) fM[ro][q] = a.M[(16 * ro + lr) * D + 16 * (q / 4) + 4 * lk + q % 4];
-    } else {
-      for (int e = tid; e < D * S::MR; e += S::kThreads) {
-        const int k = e / (4 * S::MR) * 4 + e % 4, row = e / 4 % S::MR;
-        sM[e] = row < D ? a.M[row * D + k] : 0.f;
+    sXb0 = sW + S::kVec;
+    sZb0 = sXb0 + S::kVec;
+    sE = sZb0 + S::kVec;
+    sWb = sE + S::kVec;
+    sRed = sX0 + S::kVecs * S::kVec;
+    put_at = ((2 * wave + (lk >> 1)) * S::ROWS + (lr ^ (lk & 2 ? 12 : 0))) * 8 + (lk & 1) * 4;
+    get_at = (lk * S::ROWS + (lr ^ (lk & 1 ? 12 : 0))) * 8;
+    if constexpr (BACK) Mc = (glb_f*)a.Mc;
+    if constexpr (!S::kReg) {
+      if constexpr (!BACK) {
+        for (int e = tid; e < D * S::MR; e += S::kThreads) sM[e] = a.Mc[e];
+        Mc = sM;
       }
-      for (int e = tid; e < 4 * S::kVec; e += S::kThreads) sX0[e] = 0.f;  // entries past d stay zero
+      for (int e = tid; e < S::kVecs * S::kVec; e += S::kThreads) sX0[e] = 0.f;  // entries past d stay zero
       __syncthreads();
     }
   }
 
+  __device__ __forceinline__ void load_matrices(const LtArgs& a) {
+    fA.load(a.packed, 0, wave, tid & 63);
+    fAt.load(a.packed, 1, wave, tid & 63);
+    if constexpr (S::kReg) fM.load(a.packed, 2, wave, tid & 63);
+  }
+
   // This wave's rows of column tile t into an image (the tail wave: into the FP32 tail).
-  __device__ __forceinline__ void put(uint16_t* img, float* tail, int t, f4 v) const {
-    if constexpr (KIND == kRowWave) {
+  __device__ __forceinline__ void put(lds_u16* img, lds_f* tail, int t, f4 v) const {
+    if (KIND == kRowWave || BACK) {  // (rows past d are zero)
       u2 h, m, l;
       uint32_t a0, a1, b0, b1, g0, g1;
       split_pair(v[0], v[1], a0, b0, g0);
@@ -263,26 +358,25 @@ struct LtCore {
       h = u2{a0, a1};
       m = u2{b0, b1};
       l = u2{g0, g1};
-      uint16_t* q = img + put_at + t * 16 * 8;
-      *reinterpret_cast<u2*>(q) = h;
-      *reinterpret_cast<u2*>(q + S::PIECE) = m;
-      *reinterpret_cast<u2*>(q + 2 * S::PIECE) = l;
-    } else if (lk == 0) {
-      *reinterpret_cast<f4*>(tail + (16 * t + lr) * 4) = v;
+      lds_u16* q = at<BACK>(img, put_at) + t * 16 * 8;
+      *(lds_u2*)q = h;
+      *(lds_u2*)(q + S::PIECE) = m;
+      *(lds_u2*)(q + 2 * S::PIECE) = l;
     }
+    if (KIND == kTailWave && lk == 0 && tail) st4(at<BACK>(tail, lr * 4) + 64 * t, v);
   }
 
   // Rows of this wave of (matrix) x (column tile t of the image): the small
   // products and the h h products summed apart.  `p` holds the pieces of the
   // first k-steps, read ahead.
   struct Pieces { bf8 h, m, l; };
-  static constexpr int kAhead = 2;  // k-steps read ahead
-  __device__ __forceinline__ Pieces get(const uint16_t* img, int t, int s) const {
-    const uint16_t* q = img + get_at + t * 16 * 8 + s * 32 * S::ROWS;
-    return {*reinterpret_cast<const bf8*>(q), *reinterpret_cast<const bf8*>(q + S::PIECE),
-            *reinterpret_cast<const bf8*>(q + 2 * S::PIECE)};
+  static constexpr int kAhead = BACK ? 1 : 2;  // k-steps read ahead (the reverse sweep has fewer registers to spare)
+  // (img, tail: with this lane's offset)
+  __device__ __forceinline__ Pieces get(const lds_u16* img, int t, int s) const {
+    const lds_u16* q = img + t * 16 * 8 + s * 32 * S::ROWS;
+    return {*(const lds_bf8*)q, *(const lds_bf8*)(q + S::PIECE), *(const lds_bf8*)(q + 2 * S::PIECE)};
   }
-  __device__ __forceinline__ f4 product(const Frag& F, const uint16_t* img, const float* tail, int t,
+  __device__ __forceinline__ f4 product(const Frag& F, const lds_u16* img, const lds_f* tail, int t,
                                         const Pieces (&p)[kAhead]) const {
     f4 v = f4{0.f, 0.f, 0.f, 0.f};
     if constexpr (!S::kReg) {
@@ -290,7 +384,7 @@ struct LtCore {
 #pragma unroll
       for (int s = kAhead; s < S::KB; s++) rest[s - kAhead] = get(img, t, s);
       float last = 0.f;
-      if constexpr (S::kTail) last = tail[(16 * t + lr) * 4 + lk];
+      if constexpr (S::kTail) last = tail[64 * t];
       auto piece = [&](int s) -> const Pieces& { return s < kAhead ? p[s < kAhead ? s : 0] : rest[s < kAhead ? 0 : s - kAhead]; };
 #pragma unroll
       for (int s = 0; s < S::KB; s++) {
@@ -308,12 +402,11 @@ struct LtCore {
     return v;
   }
   // The same from the state registers (d <= 32): row tile ro, column tile t.
-  __device__ __forceinline__ f4 product_reg(const float (&f)[S::kReg ? S::RPW : 1][S::kReg ? 4 * S::RPW : 1],
-                                            const f4 (&B)[RPW], int ro) const {
+  __device__ __forceinline__ f4 product_reg(const Frag& F, const f4 (&B)[RPW], int ro) const {
     f4 acc = f4{0.f, 0.f, 0.f, 0.f};
     if constexpr (S::kReg) {
 #pragma unroll
-      for (int q = 0; q < 4 * RPW; q++) acc = mfma4(f[ro][q], B[q / 4][q % 4], acc);
+      for (int q = 0; q < 4 * RPW; q++) acc = mfma4(F.f[ro][q], B[q / 4][q % 4], acc);
     }
     return acc;
   }
@@ -323,46 +416,56 @@ struct LtCore {
   // would each spend 60 instructions and two cross-lane sums on it, and hold
   // 56 registers).  d = 128: lane (lr, lk) of a row wave sums the terms
   // k = 4 lk .. 4 lk + 3 (mod 16) of row lr.
-  template <bool kRes>
-  __device__ __forceinline__ void node0(float tau, float theta, float& rx) const {
-    auto finish = [&](int i, float xn) {
-      const float xo = sX0[i], dx = xn - xo;
-      if constexpr (kRes) rx += dx * dx;
-      sX0[i] = xn;
-      sZ0[i] = xn + theta * dx;
-    };
+  // M times the vector w in LDS (entries past d zero), each entry i handed to
+  // out(i, value) by the lane that has it.
+  template <class Out>
+  __device__ __forceinline__ void gemv(const lds_f* w, const Out& out) const {
     if constexpr (S::kAux) {
       const int i = tid & 63, i2 = 64 + i < D ? 64 + i : D - 1;
-      sW[i] = sX0[i] + tau * sV[i];
-      if (64 + i < D) sW[64 + i] = sX0[64 + i] + tau * sV[64 + i];
-      __builtin_amdgcn_wave_barrier();
       float u = 0.f, v = 0.f;
-#pragma unroll 5
+      auto m = Mc;  // opaque: the addresses of the unrolled reads are not kept
+      if constexpr (BACK) asm volatile("" : "+s"(m));
+#pragma unroll(BACK ? 25 : 5)  // from global memory: all reads in flight together
       for (int k = 0; k < D; k += 4) {
-        const f4 w = *reinterpret_cast<const f4*>(sW + k);
-        const f4 a = *reinterpret_cast<const f4*>(sM + k * S::MR + 4 * i);
-        const f4 b = *reinterpret_cast<const f4*>(sM + k * S::MR + 4 * i2);
+        const f4 x = ld4(w + k);
+        const f4 a = ld4(m + k * S::MR + 4 * i);
+        const f4 b = ld4(m + k * S::MR + 4 * i2);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-          u += a[r] * w[r];
-          v += b[r] * w[r];
+          u += a[r] * x[r];
+          v += b[r] * x[r];
         }
       }
-      finish(i, u);
-      if (64 + i < D) finish(64 + i, v);
+      out(i, u);
+      if (64 + i < D) out(64 + i, v);
     } else {
       float part = 0.f;
 #pragma unroll 2
       for (int k = 4 * lk; k < D; k += 16) {
-        const f4 mm = *reinterpret_cast<const f4*>(sM + k * S::MR + 4 * (16 * wave + lr));
-        const f4 vv = *reinterpret_cast<const f4*>(sV + k);
+        const f4 mm = ld4(Mc + k * S::MR + 4 * (16 * wave + lr));
+        const f4 x = ld4(w + k);
 #pragma unroll
-        for (int r = 0; r < 4; r++) part += mm[r] * vv[r];
+        for (int r = 0; r < 4; r++) part += mm[r] * x[r];
       }
       part += __shfl_xor(part, 16, 64);
       part += __shfl_xor(part, 32, 64);
-      if (lk == 0) finish(16 * wave + lr, part);
+      if (lk == 0) out(16 * wave + lr, part);
     }
+  }
+  template <bool kRes>
+  __device__ __forceinline__ void node0(float tau, float theta, float& rx) const {
+    if constexpr (S::kAux) {
+      const int i = tid & 63;
+      sW[i] = sX0[i] + tau * sV[i];
+      if (64 + i < D) sW[64 + i] = sX0[64 + i] + tau * sV[64 + i];
+      __builtin_amdgcn_wave_barrier();
+    }
+    gemv(S::kAux ? sW : sV, [&](int i, float xn) {
+      const float xo = sX0[i], dx = xn - xo;
+      if constexpr (kRes) rx += dx * dx;
+      sX0[i] = xn;
+      sZ0[i] = xn + theta * dx;
+    });
   }
 
   // Sums over the workgroup of two values (all lanes get them).  The slots are
@@ -437,7 +540,7 @@ struct LtCore {
     put_all(imgX, tailX, X);
   }
   // A whole image, ready to be read.
-  __device__ __forceinline__ void put_all(uint16_t* img, float* tail, const Tiles& V) const {
+  __device__ __forceinline__ void put_all(lds_u16* img, lds_f* tail, const Tiles& V) const {
     if constexpr (!S::kReg) {
       if constexpr (kRows)
 #pragma unroll
@@ -449,11 +552,11 @@ struct LtCore {
   // Node 0 of this lane's rows: x_0, z_0 in the lanes lr = 0, zero in the others.
   __device__ __forceinline__ f4 x0_of(int ri) const {
     if constexpr (S::kReg) return x0[ri];
-    else return first_col(*reinterpret_cast<const f4*>(sX0 + (rows_ok(0) ? coord(0) : 0)));
+    else return first_col(ld4(sX0 + coord_now()));
   }
   __device__ __forceinline__ f4 z0_of(int ri) const {
     if constexpr (S::kReg) return z0[ri];
-    else return first_col(*reinterpret_cast<const f4*>(sZ0 + (rows_ok(0) ? coord(0) : 0)));
+    else return first_col(ld4(sZ0 + coord_now()));
   }
   __device__ __forceinline__ f4 first_col(f4 v) const {
     const bool on = lr == 0 && rows_ok(0);
@@ -471,18 +574,18 @@ struct LtCore {
       if (!rows_ok(ri)) continue;
       const int i0 = coord(ri);
       if (lr == 0) {
-        *reinterpret_cast<f4*>(dst + i0) = x0_of(ri);
-        *reinterpret_cast<f4*>(dst + CK + i0) = f4{0.f, 0.f, 0.f, 0.f};
-        *reinterpret_cast<f4*>(dst + 2 * CK + i0) = z0_of(ri);
+        st4(dst + i0, x0_of(ri));
+        st4(dst + CK + i0, f4{0.f, 0.f, 0.f, 0.f});
+        st4(dst + 2 * CK + i0, z0_of(ri));
       }
 #pragma unroll
       for (int t = 0; t < NT; t++) {
         const int j = node(t);
         if (j > Np) continue;
         float* q = dst + j * D + i0;
-        *reinterpret_cast<f4*>(q) = X[ri][t];
-        *reinterpret_cast<f4*>(q + CK) = P[ri][t];
-        *reinterpret_cast<f4*>(q + 2 * CK) = Z[ri][t];
+        st4(q, X[ri][t]);
+        st4(q + CK, P[ri][t]);
+        st4(q + 2 * CK, Z[ri][t]);
       }
     }
   }
@@ -502,13 +605,14 @@ struct LtCore {
     int np = __builtin_amdgcn_readfirstlane(Np);
     asm volatile("" : "+s"(np));
     Tiles TH;
+    const int n0 = node_now();
     if constexpr (kRows) {
       // ---- dual step: p_j <- (p_j + sigma (z_j - z_{j-1}) + lam (A x_j + eps tanh x_j)) c1 ----
       f4 zl[RPW];  // z of the node before the lane's first
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++) zl[ri] = row_prev(Z[ri][NT - 1]) + z0_of(ri);
       sweep(fA, imgX, tailX, X, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
-        const float c1t = node(t) <= np ? c1 : 0.f;  // nodes past N keep p = 0
+        const float c1t = n0 + t <= np ? c1 : 0.f;  // nodes past N keep p = 0
 #pragma unroll
         for (int ri = 0; ri < RPW; ri++) {
           const f4 zp = t > 0 ? Z[ri][t > 0 ? t - 1 : 0] : zl[ri];
@@ -523,7 +627,7 @@ struct LtCore {
             if constexpr (kRes) rp += (pn - pv) * (pn - pv);
             P[ri][t][r] = pn;
           }
-          if constexpr (S::kThLds) *reinterpret_cast<f4*>(sTh + 4 * (tid + 64 * S::RT * t)) = tht;
+          if constexpr (S::kThLds) st4(at<BACK>(sTh, 4 * tid) + 256 * S::RT * t, tht);
           else TH[ri][t] = tht;
           if constexpr (!S::kReg) put(imgP, tailP, t, P[ri][t]);
         }
@@ -531,8 +635,9 @@ struct LtCore {
       if constexpr (!S::kReg)
         if (lr == 0 && rows_ok(0)) {
           f4 v = P[0][0];
-          if constexpr (!S::kAux) v = *reinterpret_cast<const f4*>(sX0 + coord(0)) + tau * v;
-          *reinterpret_cast<f4*>(sV + coord(0)) = v;
+          const int i = coord_now();
+          if constexpr (!S::kAux) v = ld4(sX0 + i) + tau * v;
+          st4(sV + i, v);
         }
     }
     // ---- node 0: x_0 <- M (x_0 + tau p_1) --------------------------------------------
@@ -553,12 +658,12 @@ struct LtCore {
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++) pl[ri] = row_next(P[ri][0]);
       sweep(fAt, imgP, tailP, P, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
-        const float tt = node(t) < np ? tau : 0.f;  // x_N and the nodes past it do not move
+        const float tt = n0 + t < np ? tau : 0.f;  // x_N and the nodes past it do not move
 #pragma unroll
         for (int ri = 0; ri < RPW; ri++) {
           const f4 pn = t < NT - 1 ? P[ri][t < NT - 1 ? t + 1 : t] : pl[ri];
           f4 tht;
-          if constexpr (S::kThLds) tht = *reinterpret_cast<const f4*>(sTh + 4 * (tid + 64 * S::RT * t));
+          if constexpr (S::kThLds) tht = ld4(at<BACK>(sTh, 4 * tid) + 256 * S::RT * t);
           else tht = TH[ri][t];
 #pragma unroll
           for (int r = 0; r < 4; r++) {
@@ -590,7 +695,7 @@ struct LtCore {
 
   // Products of every column tile, each handed to f(t, product).
   template <class Fn>
-  __device__ __forceinline__ void sweep(const Frag& F, const uint16_t* img, const float* tail, const Tiles& B,
+  __device__ __forceinline__ void sweep(const Frag& F, const lds_u16* img, const lds_f* tail, const Tiles& B,
                                         const Fn& f) const {
     if constexpr (S::kReg) {
 #pragma unroll
@@ -599,7 +704,7 @@ struct LtCore {
 #pragma unroll
         for (int ri = 0; ri < RPW; ri++) col[ri] = B[ri][t];
 #pragma unroll
-        for (int ri = 0; ri < RPW; ri++) acc[ri] = product_reg(F.f, col, ri);
+        for (int ri = 0; ri < RPW; ri++) acc[ri] = product_reg(F, col, ri);
         f(t, acc);
         fence();
       }
@@ -607,6 +712,8 @@ struct LtCore {
       // A tile's matrix instructions are issued between the instructions of the
       // previous tile's f, one to three: a SIMD runs the two kinds one after the
       // other except for about three vector instructions behind each matrix one.
+      img = at<BACK>(img, get_at);
+      if constexpr (S::kTail) tail = at<BACK>(tail, 4 * lr + lk);
       f4 acc[1];
 #pragma unroll
       for (int t = 0; t <= NT; t++) {
@@ -618,13 +725,13 @@ struct LtCore {
         if (t < NT) next = product(F, img, tail, t, p);
         if (t > 0) f(t - 1, acc);
         if (t > 0 && t < NT) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 7, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 3 * kAhead + 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
 #pragma unroll
           for (int i = 0; i < 19; i++) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-            if (i == 2) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            if (i == 2 || (BACK && i == 8)) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
           }
         }
         fence();

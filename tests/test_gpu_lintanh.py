@@ -271,3 +271,65 @@ def test_column_tile_edges_match_oracle(oracle_mod, d, N_max):
     for got, want in ((out.x_traj, o.x_traj), (out.p_traj, o.p_traj)):
         assert traj_err(got.cpu().numpy().astype(np.float64), want, w.N).max() <= 1e-4
     lt.close()
+
+
+def _torch_phi(x, t, N, eps, A, Q, x0_all, p0_all, K, sigma, tau):
+    """phi of every point after K iterations, binary64 torch on the CPU; x0_all, p0_all: the random start."""
+    import torch
+    out = []
+    for i in range(len(N)):
+        n, d = int(N[i]), x.shape[1]
+        delta = t[i] / n
+        lam = sigma * delta
+        Qs = 0.5 * (Q + Q.T)
+        M = torch.linalg.inv(torch.eye(d, dtype=torch.float64) + tau * Qs)
+        # x_j starts at x + noise (j < N), x_N = x
+        X = torch.cat([x[i] + x0_all[i][:n], x[i][None]])
+        P = torch.cat([torch.zeros(1, d, dtype=torch.float64), p0_all[i][1:n + 1]])
+        Z = X
+        for _ in range(K):
+            th = torch.tanh(X[1:])
+            Pn = (P[1:] + sigma * (Z[1:] - Z[:-1]) + lam * (X[1:] @ A.T + eps * th)) / (1 + lam)
+            x0 = M @ (X[0] + tau * Pn[0])
+            mid = (X[1:n] - tau * (Pn[:-1] - Pn[1:])
+                   - tau * delta * (Pn[:-1] @ A + eps * (1 - th[:-1] ** 2) * Pn[:-1]))
+            Xn = torch.cat([x0[None], mid, X[n:]])
+            Z = 2 * Xn - X
+            X, P = Xn, torch.cat([P[:1], Pn])
+        f = X[1:] @ A.T + eps * torch.tanh(X[1:])
+        p = P[1:]
+        out.append(0.5 * X[0] @ Qs @ X[0] + (p * (X[1:] - X[:-1]) - delta * (0.5 * p * p - p * f)).sum())
+    return torch.stack(out)
+
+
+@pytest.mark.parametrize("d,N_max", _edge_cases())
+def test_column_tile_edges_gradients(oracle_mod, d, N_max):
+    """Gradients on both sides of the 16-node column tiles against binary64
+    autograd through the unrolled iterations (checkpoints that do not divide
+    the count, one output weight zero).  FP32 bar 1e-4."""
+    import torch
+    K, E, n = 20, 7, min(4, N_max)
+    w = _small_workload(d=d, n=n, N=N_max, K=K, seed=200 + N_max)
+    w.N = np.arange(N_max, N_max - n, -1).astype(np.int32)
+    wts = np.linspace(0.5, 1.5, n)
+    if n > 2:
+        wts[1] = 0.0
+    g = _gpu_lt(w, K, E, wts)
+    noise = [np.zeros((n, N_max + 1, d)) for _ in range(2)]
+    for i in range(n):
+        for j in range(N_max + 1):
+            for c in range(d):
+                noise[0][i, j, c] = oracle_mod.init_noise(w.init_seed, i, 0, j, c)
+                noise[1][i, j, c] = oracle_mod.init_noise(w.init_seed, i, 1, j, c)
+    T = lambda a: torch.tensor(a, dtype=torch.float64)
+    x, A, Q = T(_f32(w.x)).requires_grad_(), T(_f32(w.hp[1:])).reshape(d, d).requires_grad_(), \
+        T(_f32(w.gp)).reshape(d, d).requires_grad_()
+    eps = T(_f32(w.hp[0])).requires_grad_()
+    phi = _torch_phi(x, T(_f32(w.t)), w.N, eps, A, Q, T(noise[0]), T(noise[1]), K, float(w.sigma), float(w.tau))
+    dx, de, dA, dQ = torch.autograd.grad((phi * T(_f32(wts))).sum(), [x, eps, A, Q])
+    bar = lambda got, want: np.max(np.abs(got - want.numpy().ravel())) / max(1.0, float(want.abs().max()))
+    assert rel_err(g["phi"], phi.detach().numpy()).max() <= 1e-4
+    assert bar(g["dx"].ravel(), dx) <= 1e-4
+    assert bar(g["dh"][:1], de.reshape(1)) <= 1e-4
+    assert bar(g["dh"][1:], dA) <= 1e-4
+    assert bar(g["dg"], dQ) <= 1e-4
