@@ -182,18 +182,40 @@ __device__ __forceinline__ T group_next0(T v, int l) {
   }
 }
 
+// v + (v of the lane 16 or 32 away), by the row and half swaps of gfx950: the
+// swap of v with itself leaves both lanes of a pair with the lower one's value
+// in one register and the upper one's in the other.  A shuffle through LDS
+// held a wave that runs alone for its round trip in every iteration.
+template <int X>
+__device__ __forceinline__ auto swap_pair(uint32_t v) {
+  if constexpr (X == 16) return __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  else return __builtin_amdgcn_permlane32_swap(v, v, false, false);
+}
+template <int X>
+__device__ __forceinline__ float swap_add(float v) {
+  const auto r = swap_pair<X>(__builtin_bit_cast(uint32_t, v));
+  return __builtin_bit_cast(float, uint32_t(r[0])) + __builtin_bit_cast(float, uint32_t(r[1]));
+}
+template <int X>
+__device__ __forceinline__ double swap_add(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const auto lo = swap_pair<X>(uint32_t(b)), hi = swap_pair<X>(uint32_t(b >> 32));
+  return __builtin_bit_cast(double, (uint64_t(uint32_t(hi[0])) << 32) | uint32_t(lo[0])) +
+         __builtin_bit_cast(double, (uint64_t(uint32_t(hi[1])) << 32) | uint32_t(lo[1]));
+}
+
 // Sum over the L lanes of an aligned group (L a power of two <= 64); every
 // lane of the group receives the same total (each exchange adds a pair in
 // both lanes, and addition commutes).  Within a 16-lane row: DPP butterfly;
-// across rows: xor shuffles.
+// across rows: row and half swaps.
 template <int L, typename T>
 __device__ __forceinline__ T group_sum(T v) {
   if constexpr (L >= 2) v += dpp_f<kDppQuad1032>(v);
   if constexpr (L >= 4) v += dpp_f<kDppQuad2301>(v);
   if constexpr (L >= 8) v += dpp_f<kDppRowHalfMirror>(v);
   if constexpr (L >= 16) v += dpp_f<kDppRowMirror>(v);
-  if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
-  if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
+  if constexpr (L >= 32) v = swap_add<16>(v);
+  if constexpr (L >= 64) v = swap_add<32>(v);
   return v;
 }
 

@@ -396,7 +396,15 @@ struct Quad {
     C.dWt21 = sf * sect; C.dWt22 = cf * sect;
   }
 
-  template <typename T>
+  // v - lam g_z.  kFused: one rounding, by a fused multiply-add also where the
+  // compiler finds lam constant over a loop and would take the product out of it.
+  template <bool kFused, typename T>
+  __device__ static T gravity(const Par<T>& P, T v, T lam) {
+    if constexpr (kFused) return __builtin_elementwise_fma(-lam, P.gz, v);
+    else return v - lam * P.gz;
+  }
+
+  template <bool kFused = false, typename T>
   __device__ static void dual(const Par<T>& P, const T (&x)[12], T (&v)[12], T lam, Cache<T>& C) {
     geometry(P, x, C);
     const T w0 = x[9], w1 = x[10], w2 = x[11];
@@ -409,7 +417,7 @@ struct Quad {
     v[7] += lam * (C.W11 * w1 + C.W12 * w2);
     v[8] += lam * (C.W21 * w1 + C.W22 * w2);
     // velocity costate
-    v[5] -= lam * P.gz;
+    v[5] = gravity<kFused>(P, v[5], lam);
     const T bw = C.b[0] * v[3] + C.b[1] * v[4] + C.b[2] * v[5];
     const T bb = C.b[0] * C.b[0] + C.b[1] * C.b[1] + C.b[2] * C.b[2];
     const T coef = M<T>::div(lam * bw, T(1) + lam * bb);
@@ -477,7 +485,7 @@ struct Quad {
       v[i] += la * Sa.v[i] + lb * Sb.v[i];
       v[6 + i] += la * Sa.Ww[i] + lb * Sb.Ww[i];
     }
-    v[5] -= lam * P.gz;
+    v[5] = gravity<true>(P, v[5], lam);
     const T aa = Sa.b[0] * Sa.b[0] + Sa.b[1] * Sa.b[1] + Sa.b[2] * Sa.b[2];
     const T bb = Sb.b[0] * Sb.b[0] + Sb.b[1] * Sb.b[1] + Sb.b[2] * Sb.b[2];
     const T ab = Sa.b[0] * Sb.b[0] + Sa.b[1] * Sb.b[1] + Sa.b[2] * Sb.b[2];

@@ -17,6 +17,19 @@
 //   (sorted by N, one segment per tile class); a group whose point meets the
 //   stopping rule writes its outputs and immediately pops the next point
 //   (retire and refill), so waves stay full until the queue drains.
+//   The iterations run in an inner loop that holds nothing else, up to the next
+//   one at which a point of the wave may stop or its priority may change; the
+//   value, the stores and the refill stand outside.  The kernels are bound by
+//   instruction issue (a wave alone on its SIMD issues about nine tenths of
+//   what the SIMD can), and with the rare block inside the loop every iteration
+//   carried its control flow and the register copies that joined its paths:
+//   about 14 % of the instructions of the isaacs tiles, 5-9 % of the others.
+//   Times with the rare block inside and, where noted, all residual sums formed
+//   in every iteration, against now: 4.00 -> 3.46 ms (256 points, d = 2, FP64),
+//   1,058 -> 864 us (2,051 points, d = 3, Hopf), 48.4 -> 39.6 ms (4,099 quadrotor
+//   points), 251 -> 227 ms (65,536 points of the pursuit game), 14.4 -> 10.3 ms
+//   (Isaacs' game).  Running the body twice per trip, which would save the
+//   copies of the costates that an iteration ends with, spilled instead.
 //
 // Plain kernel
 //   One point per lane, the whole stacked state of the point in a global
@@ -50,6 +63,33 @@ inline constexpr int kFamWaves = sizeof(T) == 8 ? 1 : F::kWavesK[K];
 template <typename T, int K>
 inline constexpr int kShiftWaves = (sizeof(T) == 8 && K <= 2) ? 2 : kGroupWaves<T, K>;
 
+// Whether any lane of the wave has it, as a scalar (__any takes it through a register).
+__device__ __forceinline__ bool any_lane(bool v) { return __builtin_amdgcn_ballot_w64(v) != 0; }
+
+// Whether no point of the wave can stop by its residuals, seen from the lanes'
+// own shares: m is the largest of a lane's shares of the residuals, all of
+// which have to be below tol to stop, and s their sum.  Shares are not
+// negative and rounding keeps order, so a group's sum is at least any of its
+// lanes' shares: a group with a share of at least tol goes on, unless a share
+// is not finite (or so large that the sums could overflow; the caller then
+// forms the sums and sees).  About 15 instructions, most of them scalar, where
+// the sums of four residuals over 32 lanes take 45, in chains of dependent
+// lane exchanges; a wave alone on its SIMD waits for each of those.  Measured
+// with the sums in every iteration and so: pursuit game 254 -> 227 ms (65,536
+// points) and 34.9 -> 26.8 ms (300 points), Isaacs' game 11.7 -> 10.3 ms,
+// quadrotor 43.3 -> 39.6 ms.  The eikonal kernel, which has one residual to sum
+// and short iterations, is 2-8 % faster without and does not use it.
+template <int L, typename T>
+__device__ __forceinline__ bool goes_on(T m, T s, T tol, bool active) {
+  constexpr uint64_t kHigh = ~uint64_t(0) / (L == 64 ? ~uint64_t(0) : (uint64_t(1) << (L & 63)) - 1) << (L - 1);
+  constexpr T kBig = T(1e30);
+  const uint64_t act = __builtin_amdgcn_ballot_w64(active);
+  const uint64_t odd = __builtin_amdgcn_ballot_w64(!(s < kBig)) & act;
+  const uint64_t h = __builtin_amdgcn_ballot_w64(m >= tol) | ~act;
+  // a group (a field of L bits of h) without a bit: the classic test for a zero field
+  return (((h - (kHigh >> (L - 1))) & ~h & kHigh) | odd) == 0;
+}
+
 // Issue priority of a wave (s_setprio) from the iteration count of the
 // oldest point it holds.  A point still iterating after a tenth, a fifth and
 // two fifths of the iteration cap is in the slow tail of the batch: the few
@@ -65,11 +105,16 @@ struct WavePrio {
     t3 = 2 * (max_iter / 5) > t2 ? 2 * (max_iter / 5) : t2 + 1;
   }
   __device__ bool step(int k) const { return k == t1 || k == t2 || k == t3; }
+  // the next count after k at which something may be due: a step or the cap
+  __device__ int next(int k, int max_iter) const {
+    const int t = k < t1 ? t1 : (k < t2 ? t2 : (k < t3 ? t3 : max_iter));
+    return t < max_iter ? t : max_iter;
+  }
 };
 __device__ __forceinline__ void set_wave_priority(bool active, int k, const WavePrio& pr) {
-  if (__any(active && k >= pr.t3)) __builtin_amdgcn_s_setprio(3);
-  else if (__any(active && k >= pr.t2)) __builtin_amdgcn_s_setprio(2);
-  else if (__any(active && k >= pr.t1)) __builtin_amdgcn_s_setprio(1);
+  if (any_lane(active && k >= pr.t3)) __builtin_amdgcn_s_setprio(3);
+  else if (any_lane(active && k >= pr.t2)) __builtin_amdgcn_s_setprio(2);
+  else if (any_lane(active && k >= pr.t1)) __builtin_amdgcn_s_setprio(1);
   else __builtin_amdgcn_s_setprio(0);
 }
 
@@ -198,55 +243,141 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
   };
 
   pop_and_init();
+  int k_next = prio.next(0, a.max_iter);  // the next count at which more than an iteration is due
 
-  while (__any(active)) {
-    // ---- dual step -------------------------------------------------------
-    // z_{j-1} of the lane's first node: the previous lane's last node, or
-    // z_0 in the group's first lane (z0 is zero in every other lane; the
-    // Hopf difference operator has z_0 = 0).
-    T zprev[D];
+  while (any_lane(active)) {
+    // the iterations up to the next one that some point of the wave may stop at
+    // or the wave's priority may change at
+    bool fin, small;
+    do {
+      // ---- dual step -------------------------------------------------------
+      // z_{j-1} of the lane's first node: the previous lane's last node, or
+      // z_0 in the group's first lane (z0 is zero in every other lane; the
+      // Hopf difference operator has z_0 = 0).
+      T zprev[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) zprev[i] = group_prev_fill<L>(z[K - 1][i], l, z0[i]);
-    typename F::template Cache<T> C[K];
-    T rp = T(0), rx = T(0);
-    // kW: every node's geometry first, then the side data of the node before
-    // the lane's first (the previous lane's last node, or node 0 in the
-    // group's first lane)
-    typename SideOf<F, T, kW>::type Sp;
-    if constexpr (kW) {
+      for (int i = 0; i < D; i++) zprev[i] = group_prev_fill<L>(z[K - 1][i], l, z0[i]);
+      typename F::template Cache<T> C[K];
+      T rp = T(0), rx = T(0);
+      // kW: every node's geometry first, then the side data of the node before
+      // the lane's first (the previous lane's last node, or node 0 in the
+      // group's first lane)
+      typename SideOf<F, T, kW>::type Sp;
+      if constexpr (kW) {
 #pragma unroll
-      for (int kk = 0; kk < K; kk++) F::geometry(P, x[kk], C[kk]);
-      typename F::template Cache<T> C0;
-      F::geometry(P, x0, C0);
-      typename F::template Side<T> S0, Sl;
-      F::side(x0, C0, S0);
-      F::side(x[K - 1], C[K - 1], Sl);
-      const T m0 = (l == 0) ? T(1) : T(0);  // fill is node 0's data in the first lane, 0 elsewhere
+        for (int kk = 0; kk < K; kk++) F::geometry(P, x[kk], C[kk]);
+        typename F::template Cache<T> C0;
+        F::geometry(P, x0, C0);
+        typename F::template Side<T> S0, Sl;
+        F::side(x0, C0, S0);
+        F::side(x[K - 1], C[K - 1], Sl);
+        const T m0 = (l == 0) ? T(1) : T(0);  // fill is node 0's data in the first lane, 0 elsewhere
 #pragma unroll
-      for (int i = 0; i < 3; i++) {
-        Sp.v[i] = group_prev_fill<L>(Sl.v[i], l, m0 * S0.v[i]);
-        Sp.Ww[i] = group_prev_fill<L>(Sl.Ww[i], l, m0 * S0.Ww[i]);
-        Sp.b[i] = group_prev_fill<L>(Sl.b[i], l, m0 * S0.b[i]);
+        for (int i = 0; i < 3; i++) {
+          Sp.v[i] = group_prev_fill<L>(Sl.v[i], l, m0 * S0.v[i]);
+          Sp.Ww[i] = group_prev_fill<L>(Sl.Ww[i], l, m0 * S0.Ww[i]);
+          Sp.b[i] = group_prev_fill<L>(Sl.b[i], l, m0 * S0.b[i]);
+        }
       }
-    }
-    // Order of the lane's steps.  FP32 with four nodes per lane (Lax form):
-    // dual(0), node 0, dual(1), primal(0), dual(2), primal(1), ...,
-    // primal(K-1).  A node's primal step needs its own cache and the next
-    // node's new dual, and must follow the next node's dual step (which reads
-    // its old z), so this order keeps at most two nodes' caches live instead
-    // of K: on the quadrotor the 16x4 tile spills 79 registers instead of 103
-    // and runs 12 % faster.  Otherwise every dual step, node 0, then every
-    // primal step (the 16x3 tile compiled from the interleaved form spills
-    // less but ran 4-7 % slower; the weighted rules compute every cache
-    // first anyway; FP64 keeps its measured code).  Both orders do the same
-    // operations in the same order of the residual sums.
-    if constexpr (K >= 4 && sizeof(T) == 4 && !kW) {
-      T pnext[D];
+      // Order of the lane's steps.  FP32 with four nodes per lane (Lax form):
+      // dual(0), node 0, dual(1), primal(0), dual(2), primal(1), ...,
+      // primal(K-1).  A node's primal step needs its own cache and the next
+      // node's new dual, and must follow the next node's dual step (which reads
+      // its old z), so this order keeps at most two nodes' caches live instead
+      // of K: on the quadrotor the 16x4 tile spills 79 registers instead of 103
+      // and runs 12 % faster.  Otherwise every dual step, node 0, then every
+      // primal step (the 16x3 tile compiled from the interleaved form spills
+      // less but ran 4-7 % slower; the weighted rules compute every cache
+      // first anyway; FP64 keeps its measured code).  Both orders do the same
+      // operations in the same order of the residual sums.
+      if constexpr (K >= 4 && sizeof(T) == 4 && !kW) {
+        T pnext[D];
 #pragma unroll
-      for (int kk = 0; kk <= K; kk++) {
-        const int n = kk - 1;  // the primal step that follows dual(kk)
-        if (kk < K) {
-          // ---- dual step of node kk ------------------------------------------
+        for (int kk = 0; kk <= K; kk++) {
+          const int n = kk - 1;  // the primal step that follows dual(kk)
+          if (kk < K) {
+            // ---- dual step of node kk ------------------------------------------
+            T v[D];
+#pragma unroll
+            for (int i = 0; i < D; i++) v[i] = p[kk][i] + sigma * (z[kk][i] - (kk == 0 ? zprev[i] : z[kk - 1][i]));
+            T lam = sd;
+            if constexpr (F::kHopfGroup) {
+              if (kk == 0 && hopf) F::hopf1_in(P, v, lam, sigma, l == 0);  // node 1: with g*
+            }
+            if constexpr (kW) {
+              typename F::template Side<T> Sa, Sb;
+              if (kk == 0) Sa = Sp;
+              else F::side(x[kk - 1], C[kk - 1], Sa);
+              F::side(x[kk], C[kk], Sb);
+              F::dual_w(P, Sa, Sb, v, lam, wl, wr);
+            } else {
+              F::template dual<true>(P, x[kk], v, lam, C[kk]);
+            }
+            if constexpr (!F::kZeroSafe) {
+              // nodes past N keep p = 0
+              const int j = 1 + l * K + kk;
+#pragma unroll
+              for (int i = 0; i < D; i++) v[i] = (j <= Np) ? v[i] : T(0);
+            }
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+              const T dp = v[i] - p[kk][i];
+              rp += dp * dp;
+              p[kk][i] = v[i];
+            }
+          }
+          if (kk == 0) {
+            // ---- node 0 (after every lane's first dual step) -------------------
+#pragma unroll
+            for (int i = 0; i < D; i++) pnext[i] = group_next0<L>(p[0][i], l);
+            if (l == 0 && !hopf) {
+              T dx0[D];
+              if constexpr (kW) {
+                // proximal-gradient step: prox_{tau g}(x_0 + tau (p_1 + delta wl grad_x H(x_0, p_1)))
+                typename F::template Cache<T> C0;
+                F::geometry(P, x0, C0);
+                T g0[D], p1[D];
+                F::grad_w(P, x0, p[0], p[0], T(0), T(1), C0, g0);
+#pragma unroll
+                for (int i = 0; i < D; i++) p1[i] = p[0][i] + delta * wl * g0[i];
+                F::step0(P, x0, p1, tau, dx0);
+              } else {
+                F::step0(P, x0, p[0], tau, dx0);
+              }
+#pragma unroll
+              for (int i = 0; i < D; i++) {
+                rx += dx0[i] * dx0[i];
+                z0[i] = x0[i] + (T(1) + theta) * dx0[i];
+                x0[i] += dx0[i];
+              }
+            }
+          }
+          if (n >= 0 && n < K) {
+            // ---- primal step of node n -------------------------------------------
+            // Nodes j >= N take no step: their tau and tau*delta are 0 (x_N = x
+            // stays fixed, and past N nothing moves).
+            T g[D];
+            if constexpr (kW) {
+              T pn[D];
+#pragma unroll
+              for (int i = 0; i < D; i++) pn[i] = (n == K - 1) ? pnext[i] : p[n + 1][i];
+              F::grad_w(P, x[n], p[n], pn, wl, wr, C[n], g);
+            } else {
+              F::grad(P, x[n], p[n], C[n], g);
+            }
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+              const T pp = (n == K - 1) ? pnext[i] : p[n + 1][i];
+              const T dx = tdj[n] * g[i] - tj[n] * (p[n][i] - pp);
+              rx += dx * dx;
+              z[n][i] = x[n][i] + (T(1) + theta) * dx;
+              x[n][i] += dx;
+            }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < K; kk++) {
           T v[D];
 #pragma unroll
           for (int i = 0; i < D; i++) v[i] = p[kk][i] + sigma * (z[kk][i] - (kk == 0 ? zprev[i] : z[kk - 1][i]));
@@ -261,7 +392,7 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
             F::side(x[kk], C[kk], Sb);
             F::dual_w(P, Sa, Sb, v, lam, wl, wr);
           } else {
-            F::dual(P, x[kk], v, lam, C[kk]);
+            F::template dual<true>(P, x[kk], v, lam, C[kk]);
           }
           if constexpr (!F::kZeroSafe) {
             // nodes past N keep p = 0
@@ -276,141 +407,65 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
             p[kk][i] = v[i];
           }
         }
-        if (kk == 0) {
-          // ---- node 0 (after every lane's first dual step) -------------------
+        // ---- node 0 -----------------------------------------------------------
+        T pnext[D];
 #pragma unroll
-          for (int i = 0; i < D; i++) pnext[i] = group_next0<L>(p[0][i], l);
-          if (l == 0 && !hopf) {
-            T dx0[D];
-            if constexpr (kW) {
-              // proximal-gradient step: prox_{tau g}(x_0 + tau (p_1 + delta wl grad_x H(x_0, p_1)))
-              typename F::template Cache<T> C0;
-              F::geometry(P, x0, C0);
-              T g0[D], p1[D];
-              F::grad_w(P, x0, p[0], p[0], T(0), T(1), C0, g0);
+        for (int i = 0; i < D; i++) pnext[i] = group_next0<L>(p[0][i], l);
+        if (l == 0 && !hopf) {
+          T dx0[D];
+          if constexpr (kW) {
+            // proximal-gradient step: prox_{tau g}(x_0 + tau (p_1 + delta wl grad_x H(x_0, p_1)))
+            typename F::template Cache<T> C0;
+            F::geometry(P, x0, C0);
+            T g0[D], p1[D];
+            F::grad_w(P, x0, p[0], p[0], T(0), T(1), C0, g0);
 #pragma unroll
-              for (int i = 0; i < D; i++) p1[i] = p[0][i] + delta * wl * g0[i];
-              F::step0(P, x0, p1, tau, dx0);
-            } else {
-              F::step0(P, x0, p[0], tau, dx0);
-            }
+            for (int i = 0; i < D; i++) p1[i] = p[0][i] + delta * wl * g0[i];
+            F::step0(P, x0, p1, tau, dx0);
+          } else {
+            F::step0(P, x0, p[0], tau, dx0);
+          }
 #pragma unroll
-            for (int i = 0; i < D; i++) {
-              rx += dx0[i] * dx0[i];
-              z0[i] = x0[i] + (T(1) + theta) * dx0[i];
-              x0[i] += dx0[i];
-            }
+          for (int i = 0; i < D; i++) {
+            rx += dx0[i] * dx0[i];
+            z0[i] = x0[i] + (T(1) + theta) * dx0[i];
+            x0[i] += dx0[i];
           }
         }
-        if (n >= 0 && n < K) {
-          // ---- primal step of node n -------------------------------------------
-          // Nodes j >= N take no step: their tau and tau*delta are 0 (x_N = x
-          // stays fixed, and past N nothing moves).
+        // ---- primal step --------------------------------------------------------
+        // Nodes j >= N take no step: their tau and tau*delta are 0 (x_N = x stays
+        // fixed, and past N nothing moves).
+#pragma unroll
+        for (int kk = 0; kk < K; kk++) {
           T g[D];
           if constexpr (kW) {
             T pn[D];
 #pragma unroll
-            for (int i = 0; i < D; i++) pn[i] = (n == K - 1) ? pnext[i] : p[n + 1][i];
-            F::grad_w(P, x[n], p[n], pn, wl, wr, C[n], g);
+            for (int i = 0; i < D; i++) pn[i] = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
+            F::grad_w(P, x[kk], p[kk], pn, wl, wr, C[kk], g);
           } else {
-            F::grad(P, x[n], p[n], C[n], g);
+            F::grad(P, x[kk], p[kk], C[kk], g);
           }
 #pragma unroll
           for (int i = 0; i < D; i++) {
-            const T pp = (n == K - 1) ? pnext[i] : p[n + 1][i];
-            const T dx = tdj[n] * g[i] - tj[n] * (p[n][i] - pp);
+            const T pp = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
+            const T dx = tdj[kk] * g[i] - tj[kk] * (p[kk][i] - pp);
             rx += dx * dx;
-            z[n][i] = x[n][i] + (T(1) + theta) * dx;
-            x[n][i] += dx;
+            z[kk][i] = x[kk][i] + (T(1) + theta) * dx;
+            x[kk][i] += dx;
           }
         }
       }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < K; kk++) {
-        T v[D];
-#pragma unroll
-        for (int i = 0; i < D; i++) v[i] = p[kk][i] + sigma * (z[kk][i] - (kk == 0 ? zprev[i] : z[kk - 1][i]));
-        T lam = sd;
-        if constexpr (F::kHopfGroup) {
-          if (kk == 0 && hopf) F::hopf1_in(P, v, lam, sigma, l == 0);  // node 1: with g*
-        }
-        if constexpr (kW) {
-          typename F::template Side<T> Sa, Sb;
-          if (kk == 0) Sa = Sp;
-          else F::side(x[kk - 1], C[kk - 1], Sa);
-          F::side(x[kk], C[kk], Sb);
-          F::dual_w(P, Sa, Sb, v, lam, wl, wr);
-        } else {
-          F::dual(P, x[kk], v, lam, C[kk]);
-        }
-        if constexpr (!F::kZeroSafe) {
-          // nodes past N keep p = 0
-          const int j = 1 + l * K + kk;
-#pragma unroll
-          for (int i = 0; i < D; i++) v[i] = (j <= Np) ? v[i] : T(0);
-        }
-#pragma unroll
-        for (int i = 0; i < D; i++) {
-          const T dp = v[i] - p[kk][i];
-          rp += dp * dp;
-          p[kk][i] = v[i];
-        }
+      // ---- stopping rule (section 6 set-up) ------------------------------------
+      k++;
+      fin = true;
+      small = false;
+      if (!goes_on<L>(M<T>::fmax(rx, rp), rx + rp, a.tol, active)) {
+        const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp);
+        fin = M<T>::finite(rxs + rps);
+        small = (rxs < a.tol) && (rps < a.tol);
       }
-      // ---- node 0 -----------------------------------------------------------
-      T pnext[D];
-#pragma unroll
-      for (int i = 0; i < D; i++) pnext[i] = group_next0<L>(p[0][i], l);
-      if (l == 0 && !hopf) {
-        T dx0[D];
-        if constexpr (kW) {
-          // proximal-gradient step: prox_{tau g}(x_0 + tau (p_1 + delta wl grad_x H(x_0, p_1)))
-          typename F::template Cache<T> C0;
-          F::geometry(P, x0, C0);
-          T g0[D], p1[D];
-          F::grad_w(P, x0, p[0], p[0], T(0), T(1), C0, g0);
-#pragma unroll
-          for (int i = 0; i < D; i++) p1[i] = p[0][i] + delta * wl * g0[i];
-          F::step0(P, x0, p1, tau, dx0);
-        } else {
-          F::step0(P, x0, p[0], tau, dx0);
-        }
-#pragma unroll
-        for (int i = 0; i < D; i++) {
-          rx += dx0[i] * dx0[i];
-          z0[i] = x0[i] + (T(1) + theta) * dx0[i];
-          x0[i] += dx0[i];
-        }
-      }
-      // ---- primal step --------------------------------------------------------
-      // Nodes j >= N take no step: their tau and tau*delta are 0 (x_N = x stays
-      // fixed, and past N nothing moves).
-#pragma unroll
-      for (int kk = 0; kk < K; kk++) {
-        T g[D];
-        if constexpr (kW) {
-          T pn[D];
-#pragma unroll
-          for (int i = 0; i < D; i++) pn[i] = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
-          F::grad_w(P, x[kk], p[kk], pn, wl, wr, C[kk], g);
-        } else {
-          F::grad(P, x[kk], p[kk], C[kk], g);
-        }
-#pragma unroll
-        for (int i = 0; i < D; i++) {
-          const T pp = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
-          const T dx = tdj[kk] * g[i] - tj[kk] * (p[kk][i] - pp);
-          rx += dx * dx;
-          z[kk][i] = x[kk][i] + (T(1) + theta) * dx;
-          x[kk][i] += dx;
-        }
-      }
-    }
-    // ---- stopping rule (section 6 set-up) ------------------------------------
-    k++;
-    const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp);
-    const bool fin = M<T>::finite(rxs + rps);
-    const bool small = (rxs < a.tol) && (rps < a.tol);
+    } while (!any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     const bool done = active && (!fin || (!a.fixed && small) || k >= a.max_iter);
     if (done) {
       // value: Lagrangian at the last iterate (Algorithm 1)
@@ -481,7 +536,8 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
       }
       pop_and_init();
     }
-    if (__any(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
+    k_next = prio.next(k, a.max_iter);
+    if (any_lane(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
   }
 }
 
@@ -893,116 +949,123 @@ __global__ void __launch_bounds__(256, (kShiftWaves<T, K>)) k_group_control_shif
   };
 
   pop_and_init();
+  int k_next = prio.next(0, a.max_iter);  // the next count at which more than an iteration is due
 
-  while (__any(active)) {
-    // ---- speeds at the current iterate (own primal slots) --------------------
-    T cj[K], gc0[K], gc1[K];
+  while (any_lane(active)) {
+    // the iterations up to the next one that some point of the wave may stop at
+    // or the wave's priority may change at
+    bool fin, small;
+    do {
+      // ---- speeds at the current iterate (own primal slots) --------------------
+      T cj[K], gc0[K], gc1[K];
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) F::speed(P, x[kk], cj[kk], gc0[kk], gc1[kk]);
-    // right neighbour of the last slot: next lane's slot 0, or x in the last lane
-    T znext[D];
+      for (int kk = 0; kk < K; kk++) F::speed(P, x[kk], cj[kk], gc0[kk], gc1[kk]);
+      // right neighbour of the last slot: next lane's slot 0, or x in the last lane
+      T znext[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) znext[i] = group_next0<L>(z[0][i], l) + xe[i];
-    const T cnext = group_next0<L>(cj[0], l) + ce;
-    // ---- dual step: tau p_{j+1} in slot kk -------------------------------------
-    T pn[K];  // tau |p_{j+1}|
-    T pold[K][D];
-    T rp = T(0), rx = T(0);
+      for (int i = 0; i < D; i++) znext[i] = group_next0<L>(z[0][i], l) + xe[i];
+      const T cnext = group_next0<L>(cj[0], l) + ce;
+      // ---- dual step: tau p_{j+1} in slot kk -------------------------------------
+      T pn[K];  // tau |p_{j+1}|
+      T pold[K][D];
+      T rp = T(0), rx = T(0);
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      T v[D];
+      for (int kk = 0; kk < K; kk++) {
+        T v[D];
 #pragma unroll
-      for (int i = 0; i < D; i++) v[i] = ps[kk][i] + ts * ((kk == K - 1 ? znext[i] : z[kk + 1][i]) - z[kk][i]);
-      // interval (j, j+1): speed of its right node; the weighted rule mixes
-      // in its left node's (this slot's own primal node)
-      const T cr = kMix ? wl * cj[kk] + wr * ((kk == K - 1) ? cnext : cj[kk + 1])
-                        : ((kk == K - 1) ? cnext : cj[kk + 1]);
-      if constexpr (kHopf) {
-        if (kk == 0) pn[kk] = F::shrink_hopf1(P, v, tsd * cr, sigma, first, tau);  // node 1: with g*
-        else pn[kk] = F::shrink(v, tsd * cr);
-      } else {
-        pn[kk] = F::shrink(v, tsd * cr);
-      }
-#pragma unroll
-      for (int i = 0; i < D; i++) {
-        if constexpr (kLazyRp) {
-          pold[kk][i] = ps[kk][i];
+        for (int i = 0; i < D; i++) v[i] = ps[kk][i] + ts * ((kk == K - 1 ? znext[i] : z[kk + 1][i]) - z[kk][i]);
+        // interval (j, j+1): speed of its right node; the weighted rule mixes
+        // in its left node's (this slot's own primal node)
+        const T cr = kMix ? wl * cj[kk] + wr * ((kk == K - 1) ? cnext : cj[kk + 1])
+                          : ((kk == K - 1) ? cnext : cj[kk + 1]);
+        if constexpr (kHopf) {
+          if (kk == 0) pn[kk] = F::shrink_hopf1(P, v, tsd * cr, sigma, first, tau);  // node 1: with g*
+          else pn[kk] = F::shrink(v, tsd * cr);
         } else {
-          const T dp = v[i] - ps[kk][i];
-          rp += dp * dp;
+          pn[kk] = F::shrink(v, tsd * cr);
         }
-        ps[kk][i] = v[i];
-      }
-    }
-    // ---- primal step: x_j in slot kk; p_j of the first slot from the previous
-    //      lane (p_0 = 0 in the first lane) --------------------------------------
-    T pprev[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) pprev[i] = group_prev0<L>(ps[K - 1][i], l);
-    const T pnprev = group_prev0<L>(pn[K - 1], l);
-#pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      // tau delta |p_j| (interval (j-1, j)); the weighted rule takes
-      // tau delta (wr |p_j| + wl |p_{j+1}|), x_j bounding both intervals
-      const T pj = (kk == 0) ? pnprev : pn[kk - 1];
-      const T coef = kMix ? delta * (wr * pj + wl * pn[kk]) : delta * pj;
-      T dx[D];
-#pragma unroll
-      for (int i = 0; i < D; i++) dx[i] = ps[kk][i] - ((kk == 0) ? pprev[i] : ps[kk - 1][i]);
-      dx[0] += coef * gc0[kk];
-      dx[1] += coef * gc1[kk];
-      if constexpr (!kHopf) {
-        if (kk == 0) {
-          // node 0 (first lane): the prox of g after the step
-          if (aff0) {
-#pragma unroll
-            for (int i = 0; i < D; i++) dx[i] = m0 * dx[i] + (mm0 * x[0][i] + f0[i]);
+        for (int i = 0; i < D; i++) {
+          if constexpr (kLazyRp) {
+            pold[kk][i] = ps[kk][i];
           } else {
-            T v[D];
-#pragma unroll
-            for (int i = 0; i < D; i++) v[i] = x[0][i] + dx[i];
-            F::prox0(P, v, tau, first);
-#pragma unroll
-            for (int i = 0; i < D; i++) dx[i] = v[i] - x[0][i];
-          }
-        }
-      }
-      T sx = T(0);
-#pragma unroll
-      for (int i = 0; i < D; i++) {
-        sx += dx[i] * dx[i];
-        x[kk][i] += mv[kk] * dx[i];
-        z[kk][i] = x[kk][i] + mz[kk] * dx[i];
-      }
-      rx += mv[kk] * sx;
-    }
-    // ---- stopping rule (section 6 set-up) ------------------------------------
-    k++;
-    // Lazy form: the p residual decides only where the x residual is already
-    // below tol, so it is formed (from the stored iterates) only when some
-    // group of the wave gets there, and is 0 otherwise.
-    const T rxs = group_sum<L>(rx);
-    T rps = T(0);
-    if constexpr (kLazyRp) {
-      if (__any(active && rxs < a.tol)) {
-#pragma unroll
-        for (int kk = 0; kk < K; kk++)
-#pragma unroll
-          for (int i = 0; i < D; i++) {
-            const T dp = ps[kk][i] - pold[kk][i];
+            const T dp = v[i] - ps[kk][i];
             rp += dp * dp;
           }
+          ps[kk][i] = v[i];
+        }
+      }
+      // ---- primal step: x_j in slot kk; p_j of the first slot from the previous
+      //      lane (p_0 = 0 in the first lane) --------------------------------------
+      T pprev[D];
+#pragma unroll
+      for (int i = 0; i < D; i++) pprev[i] = group_prev0<L>(ps[K - 1][i], l);
+      const T pnprev = group_prev0<L>(pn[K - 1], l);
+#pragma unroll
+      for (int kk = 0; kk < K; kk++) {
+        // tau delta |p_j| (interval (j-1, j)); the weighted rule takes
+        // tau delta (wr |p_j| + wl |p_{j+1}|), x_j bounding both intervals
+        const T pj = (kk == 0) ? pnprev : pn[kk - 1];
+        const T coef = kMix ? delta * (wr * pj + wl * pn[kk]) : delta * pj;
+        T dx[D];
+#pragma unroll
+        for (int i = 0; i < D; i++) dx[i] = ps[kk][i] - ((kk == 0) ? pprev[i] : ps[kk - 1][i]);
+        dx[0] += coef * gc0[kk];
+        dx[1] += coef * gc1[kk];
+        if constexpr (!kHopf) {
+          if (kk == 0) {
+            // node 0 (first lane): the prox of g after the step
+            if (aff0) {
+#pragma unroll
+              for (int i = 0; i < D; i++) dx[i] = m0 * dx[i] + (mm0 * x[0][i] + f0[i]);
+            } else {
+              T v[D];
+#pragma unroll
+              for (int i = 0; i < D; i++) v[i] = x[0][i] + dx[i];
+              F::prox0(P, v, tau, first);
+#pragma unroll
+              for (int i = 0; i < D; i++) dx[i] = v[i] - x[0][i];
+            }
+          }
+        }
+        T sx = T(0);
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+          sx += dx[i] * dx[i];
+          x[kk][i] += mv[kk] * dx[i];
+          z[kk][i] = x[kk][i] + mz[kk] * dx[i];
+        }
+        rx += mv[kk] * sx;
+      }
+      // ---- stopping rule (section 6 set-up) ------------------------------------
+      k++;
+      // Lazy form: the p residual decides only where the x residual is already
+      // below tol, so it is formed (from the stored iterates) only when some
+      // group of the wave gets there, and is 0 otherwise.
+      const T rxs = group_sum<L>(rx);
+      T rps = T(0);
+      if constexpr (kLazyRp) {
+        if (any_lane(active && rxs < a.tol)) {
+#pragma unroll
+          for (int kk = 0; kk < K; kk++)
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+              const T dp = ps[kk][i] - pold[kk][i];
+              rp += dp * dp;
+            }
+          rps = group_sum<L>(rp);
+        }
+      } else {
         rps = group_sum<L>(rp);
       }
-    } else {
-      rps = group_sum<L>(rp);
-    }
-    const bool fin = M<T>::finite(rxs + rps);
-    const bool small = (rxs < a.tol) && (rps < tolp);
+      fin = M<T>::finite(rxs + rps);
+      small = (rxs < a.tol) && (rps < tolp);
+    } while (!any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     const bool done = active && (!fin || (!a.fixed && small) || k >= a.max_iter);
     if (done) {
       // value: g(x_0) + sum_j <p_j, x_j - x_{j-1}> - delta sum_j c(x_j) |p_j|,
       // the sum taken over tau p and scaled back
+      T cj[K], gc0[K], gc1[K];
 #pragma unroll
       for (int kk = 0; kk < K; kk++) F::speed(P, x[kk], cj[kk], gc0[kk], gc1[kk]);
       const T cn2 = group_next0<L>(cj[0], l) + ce;
@@ -1074,7 +1137,8 @@ __global__ void __launch_bounds__(256, (kShiftWaves<T, K>)) k_group_control_shif
       }
       pop_and_init();
     }
-    if (__any(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
+    k_next = prio.next(k, a.max_iter);
+    if (any_lane(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
   }
 }
 
@@ -1223,106 +1287,116 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_game(KArgs<
   };
 
   pop_and_init();
+  int k_next = prio.next(0, a.max_iter);  // the next count at which more than an iteration is due
 
-  while (__any(active)) {
-    T zprev[DX], wprev[DY];
+  while (any_lane(active)) {
+    // the iterations up to the next one that some point of the wave may stop at
+    // or the wave's priority may change at
+    bool fin, small;
+    do {
+      T zprev[DX], wprev[DY];
 #pragma unroll
-    for (int i = 0; i < DX; i++) zprev[i] = group_prev_fill<L>(z[K - 1][i], l, z0[i]);
+      for (int i = 0; i < DX; i++) zprev[i] = group_prev_fill<L>(z[K - 1][i], l, z0[i]);
 #pragma unroll
-    for (int i = 0; i < DY; i++) wprev[i] = group_prev_fill<L>(w[K - 1][i], l, w0[i]);
-    typename F::template CacheX<T> CX[K];
-    typename F::template CacheY<T> CY[K];
-    T rp = T(0), rq = T(0), rx = T(0), ry = T(0);
-    // ---- p block, then q block ----------------------------------------------
+      for (int i = 0; i < DY; i++) wprev[i] = group_prev_fill<L>(w[K - 1][i], l, w0[i]);
+      typename F::template CacheX<T> CX[K];
+      typename F::template CacheY<T> CY[K];
+      T rp = T(0), rq = T(0), rx = T(0), ry = T(0);
+      // ---- p block, then q block ----------------------------------------------
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      T v[DX];
+      for (int kk = 0; kk < K; kk++) {
+        T v[DX];
 #pragma unroll
-      for (int i = 0; i < DX; i++) v[i] = p[kk][i] + sigma * (z[kk][i] - (kk == 0 ? zprev[i] : z[kk - 1][i]));
-      F::dual_p(P, x[kk], v, sdj[kk], ipj[kk], CX[kk]);
-      T u[DY];
+        for (int i = 0; i < DX; i++) v[i] = p[kk][i] + sigma * (z[kk][i] - (kk == 0 ? zprev[i] : z[kk - 1][i]));
+        F::dual_p(P, x[kk], v, sdj[kk], ipj[kk], CX[kk]);
+        T u[DY];
 #pragma unroll
-      for (int i = 0; i < DY; i++) u[i] = q[kk][i] + sigma * (w[kk][i] - (kk == 0 ? wprev[i] : w[kk - 1][i]));
-      F::dual_q(P, y[kk], u, sdj[kk], iqj[kk], CY[kk]);
-      // nodes past N: v = u = 0 and the step leaves them at 0 (p = q = 0 stays, no residual)
+        for (int i = 0; i < DY; i++) u[i] = q[kk][i] + sigma * (w[kk][i] - (kk == 0 ? wprev[i] : w[kk - 1][i]));
+        F::dual_q(P, y[kk], u, sdj[kk], iqj[kk], CY[kk]);
+        // nodes past N: v = u = 0 and the step leaves them at 0 (p = q = 0 stays, no residual)
 #pragma unroll
-      for (int i = 0; i < DX; i++) {
-        const T dp = v[i] - p[kk][i];
-        rp += dp * dp;
-        p[kk][i] = v[i];
+        for (int i = 0; i < DX; i++) {
+          const T dp = v[i] - p[kk][i];
+          rp += dp * dp;
+          p[kk][i] = v[i];
+        }
+#pragma unroll
+        for (int i = 0; i < DY; i++) {
+          const T dq = u[i] - q[kk][i];
+          rq += dq * dq;
+          q[kk][i] = u[i];
+        }
       }
+      T pnext[DX], qnext[DY];
 #pragma unroll
-      for (int i = 0; i < DY; i++) {
-        const T dq = u[i] - q[kk][i];
-        rq += dq * dq;
-        q[kk][i] = u[i];
+      for (int i = 0; i < DX; i++) pnext[i] = group_next0<L>(p[0][i], l);
+#pragma unroll
+      for (int i = 0; i < DY; i++) qnext[i] = group_next0<L>(q[0][i], l);
+      // ---- node 0 (the group's first lane): x_0 by the prox of g(., y_0^k), then
+      //      y_0 by the prox of -g(x_0^{k+1}, .), in one branch (neither depends
+      //      on the other nodes' primal steps).  A branch, not masked arithmetic
+      //      in every lane: measured, the branch costs the wave less.
+      if (l == 0) {
+        T v0[DX], xn0[DX], u0[DY], yn0[DY];
+#pragma unroll
+        for (int i = 0; i < DX; i++) v0[i] = x0[i] + tau * p[0][i];
+        F::prox_x0(P, v0, y0, tau, xn0);
+#pragma unroll
+        for (int i = 0; i < DY; i++) u0[i] = y0[i] + tau * q[0][i];
+        F::stretch_y0(P, u0, xn0, tau, yn0);
+#pragma unroll
+        for (int i = 0; i < DX; i++) {
+          const T dx = xn0[i] - x0[i];
+          rx += dx * dx;
+          z0[i] = xn0[i] + theta * dx;
+          x0[i] = xn0[i];
+        }
+#pragma unroll
+        for (int i = 0; i < DY; i++) {
+          const T dy = yn0[i] - y0[i];
+          ry += dy * dy;
+          w0[i] = yn0[i] + theta * dy;
+          y0[i] = yn0[i];
+        }
       }
-    }
-    T pnext[DX], qnext[DY];
+      // ---- x block: descent steps ---------------------------------------------------
 #pragma unroll
-    for (int i = 0; i < DX; i++) pnext[i] = group_next0<L>(p[0][i], l);
+      for (int kk = 0; kk < K; kk++) {
+        T g[DX];
+        F::grad_x(P, x[kk], p[kk], CX[kk], g);
 #pragma unroll
-    for (int i = 0; i < DY; i++) qnext[i] = group_next0<L>(q[0][i], l);
-    // ---- node 0 (the group's first lane): x_0 by the prox of g(., y_0^k), then
-    //      y_0 by the prox of -g(x_0^{k+1}, .), in one branch (neither depends
-    //      on the other nodes' primal steps).  A branch, not masked arithmetic
-    //      in every lane: measured, the branch costs the wave less.
-    if (l == 0) {
-      T v0[DX], xn0[DX], u0[DY], yn0[DY];
-#pragma unroll
-      for (int i = 0; i < DX; i++) v0[i] = x0[i] + tau * p[0][i];
-      F::prox_x0(P, v0, y0, tau, xn0);
-#pragma unroll
-      for (int i = 0; i < DY; i++) u0[i] = y0[i] + tau * q[0][i];
-      F::stretch_y0(P, u0, xn0, tau, yn0);
-#pragma unroll
-      for (int i = 0; i < DX; i++) {
-        const T dx = xn0[i] - x0[i];
-        rx += dx * dx;
-        z0[i] = xn0[i] + theta * dx;
-        x0[i] = xn0[i];
+        for (int i = 0; i < DX; i++) {
+          const T pp = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
+          const T dx = tdj[kk] * g[i] - tj[kk] * (p[kk][i] - pp);
+          rx += dx * dx;
+          z[kk][i] = x[kk][i] + (T(1) + theta) * dx;
+          x[kk][i] += dx;
+        }
       }
+      // ---- y block: ascent steps -----------------------------------------------------
 #pragma unroll
-      for (int i = 0; i < DY; i++) {
-        const T dy = yn0[i] - y0[i];
-        ry += dy * dy;
-        w0[i] = yn0[i] + theta * dy;
-        y0[i] = yn0[i];
+      for (int kk = 0; kk < K; kk++) {
+        T g[DY];
+        F::grad_y(P, y[kk], q[kk], CY[kk], g);
+#pragma unroll
+        for (int i = 0; i < DY; i++) {
+          const T qq = (kk == K - 1) ? qnext[i] : q[kk + 1][i];
+          const T dy = -tdj[kk] * g[i] - tj[kk] * (q[kk][i] - qq);
+          ry += dy * dy;
+          w[kk][i] = y[kk][i] + (T(1) + theta) * dy;
+          y[kk][i] += dy;
+        }
       }
-    }
-    // ---- x block: descent steps ---------------------------------------------------
-#pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      T g[DX];
-      F::grad_x(P, x[kk], p[kk], CX[kk], g);
-#pragma unroll
-      for (int i = 0; i < DX; i++) {
-        const T pp = (kk == K - 1) ? pnext[i] : p[kk + 1][i];
-        const T dx = tdj[kk] * g[i] - tj[kk] * (p[kk][i] - pp);
-        rx += dx * dx;
-        z[kk][i] = x[kk][i] + (T(1) + theta) * dx;
-        x[kk][i] += dx;
+      // ---- stopping rule ------------------------------------------------------------
+      k++;
+      fin = true;
+      small = false;
+      if (kRec || !goes_on<L>(M<T>::fmax(M<T>::fmax(rx, rp), M<T>::fmax(ry, rq)), (rx + rp) + (ry + rq), a.tol, active)) {
+        const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp), rys = group_sum<L>(ry), rqs = group_sum<L>(rq);
+        fin = M<T>::finite(rxs + rps + rys + rqs);
+        small = (rxs < a.tol) && (rps < a.tol) && (rys < a.tol) && (rqs < a.tol);
       }
-    }
-    // ---- y block: ascent steps -----------------------------------------------------
-#pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      T g[DY];
-      F::grad_y(P, y[kk], q[kk], CY[kk], g);
-#pragma unroll
-      for (int i = 0; i < DY; i++) {
-        const T qq = (kk == K - 1) ? qnext[i] : q[kk + 1][i];
-        const T dy = -tdj[kk] * g[i] - tj[kk] * (q[kk][i] - qq);
-        ry += dy * dy;
-        w[kk][i] = y[kk][i] + (T(1) + theta) * dy;
-        y[kk][i] += dy;
-      }
-    }
-    // ---- stopping rule ------------------------------------------------------------
-    k++;
-    const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp), rys = group_sum<L>(ry), rqs = group_sum<L>(rq);
-    const bool fin = M<T>::finite(rxs + rps + rys + rqs);
-    const bool small = (rxs < a.tol) && (rps < a.tol) && (rys < a.tol) && (rqs < a.tol);
+    } while (!kRec && !any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     bool done;
     int st = kMaxIter;
     if constexpr (!kRec) {
@@ -1440,7 +1514,8 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_game(KArgs<
       }
       pop_and_init();
     }
-    if (__any(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
+    if constexpr (!kRec) k_next = prio.next(k, a.max_iter);
+    if (any_lane(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
   }
 }
 
@@ -1517,73 +1592,83 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_game_hopf(K
   };
 
   pop_and_init();
+  int k_next = prio.next(0, a.max_iter);  // the next count at which more than an iteration is due
 
-  while (__any(active)) {
-    // z_{j-1}, w_{j-1} of the lane's first node; in the group's first lane
-    // node 0's (zero in the Hopf formulation, which has no node 0)
-    const T zprev = group_prev_fill<L>(z[K - 1], l, z0), wprev = group_prev_fill<L>(w[K - 1], l, w0);
-    T gx[K];  // d c/dx at (x^k, y^k)
-    T rp = T(0), rq = T(0), rx = T(0), ry = T(0);
-    // ---- p, then q, node by node ------------------------------------------------
+  while (any_lane(active)) {
+    // the iterations up to the next one that some point of the wave may stop at
+    // or the wave's priority may change at
+    bool fin, small;
+    do {
+      // z_{j-1}, w_{j-1} of the lane's first node; in the group's first lane
+      // node 0's (zero in the Hopf formulation, which has no node 0)
+      const T zprev = group_prev_fill<L>(z[K - 1], l, z0), wprev = group_prev_fill<L>(w[K - 1], l, w0);
+      T gx[K];  // d c/dx at (x^k, y^k)
+      T rp = T(0), rq = T(0), rx = T(0), ry = T(0);
+      // ---- p, then q, node by node ------------------------------------------------
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      const int j = 1 + l * K + kk;
-      const bool first = !kLax && (l == 0) && (kk == 0);  // Hopf node 1: with e* and h_*
-      T dcy;
-      const T c = F::speed(P, x[kk], y[kk], gx[kk], dcy);
-      const T v = p[kk] + sigma * (z[kk] - (kk == 0 ? zprev : z[kk - 1]));
-      const T pn = F::dual_p(P, p[kk], q[kk], v, sd, sigma, first);
-      const T u = q[kk] + sigma * (w[kk] - (kk == 0 ? wprev : w[kk - 1]));
-      const T qn = F::dual_q(P, c, pn, q[kk], u, sd, sigma, first);
-      if (j <= Np) {
-        rp += (pn - p[kk]) * (pn - p[kk]);
-        rq += (qn - q[kk]) * (qn - q[kk]);
-        p[kk] = pn;
-        q[kk] = qn;
+      for (int kk = 0; kk < K; kk++) {
+        const int j = 1 + l * K + kk;
+        const bool first = !kLax && (l == 0) && (kk == 0);  // Hopf node 1: with e* and h_*
+        T dcy;
+        const T c = F::speed(P, x[kk], y[kk], gx[kk], dcy);
+        const T v = p[kk] + sigma * (z[kk] - (kk == 0 ? zprev : z[kk - 1]));
+        const T pn = F::dual_p(P, p[kk], q[kk], v, sd, sigma, first);
+        const T u = q[kk] + sigma * (w[kk] - (kk == 0 ? wprev : w[kk - 1]));
+        const T qn = F::dual_q(P, c, pn, q[kk], u, sd, sigma, first);
+        if (j <= Np) {
+          rp += (pn - p[kk]) * (pn - p[kk]);
+          rq += (qn - q[kk]) * (qn - q[kk]);
+          p[kk] = pn;
+          q[kk] = qn;
+        }
       }
-    }
-    const T pnext = group_next0<L>(p[0], l), qnext = group_next0<L>(q[0], l);
-    // ---- x: node 0 by the prox of e (Algorithm 3), then descent, grad_x H(x, y, p, -q) = q dc/dx
-    if constexpr (kLax) {
-      if (l == 0) {
-        const T dx0 = F::prox_e(P, x0 + tau * p[0], tau) - x0;
-        rx += dx0 * dx0;
-        z0 = x0 + (T(1) + theta) * dx0;
-        x0 += dx0;
+      const T pnext = group_next0<L>(p[0], l), qnext = group_next0<L>(q[0], l);
+      // ---- x: node 0 by the prox of e (Algorithm 3), then descent, grad_x H(x, y, p, -q) = q dc/dx
+      if constexpr (kLax) {
+        if (l == 0) {
+          const T dx0 = F::prox_e(P, x0 + tau * p[0], tau) - x0;
+          rx += dx0 * dx0;
+          z0 = x0 + (T(1) + theta) * dx0;
+          x0 += dx0;
+        }
       }
-    }
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      const T pp = (kk == K - 1) ? pnext : p[kk + 1];
-      const T dx = tdj[kk] * q[kk] * gx[kk] - tj[kk] * (p[kk] - pp);
-      rx += dx * dx;
-      z[kk] = x[kk] + (T(1) + theta) * dx;
-      x[kk] += dx;
-    }
-    // ---- y: node 0 by the prox of -h (Algorithm 3), then ascent at the new x ---------
-    if constexpr (kLax) {
-      if (l == 0) {
-        const T dy0 = F::prox_mh(P, y0 + tau * q[0], tau) - y0;
-        ry += dy0 * dy0;
-        w0 = y0 + (T(1) + theta) * dy0;
-        y0 += dy0;
+      for (int kk = 0; kk < K; kk++) {
+        const T pp = (kk == K - 1) ? pnext : p[kk + 1];
+        const T dx = tdj[kk] * q[kk] * gx[kk] - tj[kk] * (p[kk] - pp);
+        rx += dx * dx;
+        z[kk] = x[kk] + (T(1) + theta) * dx;
+        x[kk] += dx;
       }
-    }
+      // ---- y: node 0 by the prox of -h (Algorithm 3), then ascent at the new x ---------
+      if constexpr (kLax) {
+        if (l == 0) {
+          const T dy0 = F::prox_mh(P, y0 + tau * q[0], tau) - y0;
+          ry += dy0 * dy0;
+          w0 = y0 + (T(1) + theta) * dy0;
+          y0 += dy0;
+        }
+      }
 #pragma unroll
-    for (int kk = 0; kk < K; kk++) {
-      T dcx, dcy;
-      (void)F::speed(P, x[kk], y[kk], dcx, dcy);
-      const T qq = (kk == K - 1) ? qnext : q[kk + 1];
-      const T dy = -tdj[kk] * q[kk] * dcy - tj[kk] * (q[kk] - qq);
-      ry += dy * dy;
-      w[kk] = y[kk] + (T(1) + theta) * dy;
-      y[kk] += dy;
-    }
-    // ---- stopping rule: all four blocks -------------------------------------------
-    k++;
-    const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp), rys = group_sum<L>(ry), rqs = group_sum<L>(rq);
-    const bool fin = M<T>::finite(rxs + rps + rys + rqs);
-    const bool small = (rxs < a.tol) && (rps < a.tol) && (rys < a.tol) && (rqs < a.tol);
+      for (int kk = 0; kk < K; kk++) {
+        T dcx, dcy;
+        (void)F::speed(P, x[kk], y[kk], dcx, dcy);
+        const T qq = (kk == K - 1) ? qnext : q[kk + 1];
+        const T dy = -tdj[kk] * q[kk] * dcy - tj[kk] * (q[kk] - qq);
+        ry += dy * dy;
+        w[kk] = y[kk] + (T(1) + theta) * dy;
+        y[kk] += dy;
+      }
+      // ---- stopping rule: all four blocks -------------------------------------------
+      k++;
+      fin = true;
+      small = false;
+      if (!goes_on<L>(M<T>::fmax(M<T>::fmax(rx, rp), M<T>::fmax(ry, rq)), (rx + rp) + (ry + rq), a.tol, active)) {
+        const T rxs = group_sum<L>(rx), rps = group_sum<L>(rp), rys = group_sum<L>(ry), rqs = group_sum<L>(rq);
+        fin = M<T>::finite(rxs + rps + rys + rqs);
+        small = (rxs < a.tol) && (rps < a.tol) && (rys < a.tol) && (rqs < a.tol);
+      }
+    } while (!any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     const bool done = active && (!fin || (!a.fixed && small) || k >= a.max_iter);
     if (done) {
       const T xprev = group_prev_fill<L>(x[K - 1], l, x0), yprev = group_prev_fill<L>(y[K - 1], l, y0);
@@ -1646,7 +1731,8 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_game_hopf(K
       }
       pop_and_init();
     }
-    if (__any(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
+    k_next = prio.next(k, a.max_iter);
+    if (any_lane(done || (active && prio.step(k)))) set_wave_priority(active, k, prio);
   }
 }
 
