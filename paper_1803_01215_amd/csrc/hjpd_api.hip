@@ -227,6 +227,8 @@ struct Cls {
   int lo, hi, L, K;
   const void* kern;
   int grid;  // persistent grid (blocks of 256)
+  const void* split = nullptr;  // the same sums on twice the lanes, one node each (small batches), or null
+  int split_grid = 0;
 };
 
 // Device scratch of one solve: the bucket counters and cursors, the class
@@ -362,20 +364,34 @@ int persistent_grid(hjpd_ctx* c, const void* kern) {
 constexpr int kTailBlocksPerCU = 2;
 constexpr int64_t kBulkFactor = 8;
 
-int launch_grid(const hjpd_ctx* c, const Cls& cl, int64_t n) {
-  const int per_block = 256 / cl.L;                          // points one block holds at once
+int launch_grid(const hjpd_ctx* c, int L, int full, int64_t n) {
+  const int per_block = 256 / L;                             // points one block holds at once
   // without refill every group takes one point: enough groups for the whole
   // batch (an upper bound on the class), each block leaving when its groups finish
   if (c->desc.flags & HJPD_NO_REFILL) return int(std::max<int64_t>(1, (n + per_block - 1) / per_block));
-  const int64_t resident = int64_t(cl.grid) * per_block;     // points held at once, full occupancy
-  int64_t grid = cl.grid;
+  const int64_t resident = int64_t(full) * per_block;        // points held at once, full occupancy
+  int64_t grid = full;
   if (n <= kBulkFactor * resident) {
-    const int nb = cl.grid / c->n_cu;
+    const int nb = full / c->n_cu;
     grid = int64_t(nb < kTailBlocksPerCU ? nb : kTailBlocksPerCU) * c->n_cu;
   }
   const int64_t fill = (n + per_block - 1) / per_block;
   if (grid > fill) grid = fill > 0 ? fill : 1;
   return int(grid);
+}
+
+// Whether a class runs its split tile (twice the lanes per point, one node
+// each, the same results): while the whole batch in it makes at most
+// kSplitWavesPerCU waves per CU.  Fewer points end sooner, since the slowest
+// ones take 1.6 times less time an iteration; more of them fill the SIMDs, and
+// then two nodes per lane, which share a point's exchanges and tests, win.
+// Quadrotor, N up to 60, two nodes against split: 25.7 / 16.8 ms (64 points),
+// 26.4 / 17.0 (500), 39.5 / 32.0 (3,000 points, 12 waves per CU of 64 lanes),
+// 39.7 / 39.1 (4,099; in another batch of that size 40.2 / 43.5), 39.9 / 41.3
+// (4,600), 45.0 / 49.5 (6,000), 97.1 / 105.7 (16,384).
+constexpr int kSplitWavesPerCU = 12;
+bool use_split(const hjpd_ctx* c, const Cls& cl, int64_t n) {
+  return cl.split && n * (2 * cl.L) <= int64_t(64) * kSplitWavesPerCU * c->n_cu;
 }
 
 void drop_graph(hjpd_ctx* c);
@@ -402,6 +418,10 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec) {
     cl.kern = lk(0, cs.L, cs.K, kernel_variant(D));
     if (!cl.kern) return fail(HJPD_EUNSUPPORTED, "plan: tile not built");
     cl.grid = persistent_grid(c, cl.kern);
+    // a tile asked for by the descriptor is the one that runs
+    if (cs.K == 2 && (cs.L == 16 || cs.L == 32) && kernel_variant(D) == hjpd::kVarPlain && D.lanes_per_point == 0)
+      cl.split = lk(0, 2 * cs.L, 1, hjpd::kVarSplit);
+    if (cl.split) cl.split_grid = persistent_grid(c, cl.split);
     plan.push_back(cl);
     prev = cl.hi;
     if (prev >= D.N_max) break;
@@ -701,7 +721,10 @@ int enqueue_solve(hjpd_ctx* c, const Workspace& ws, int64_t n, const void* x, co
       if (st != s) HIP_OK(hipStreamWaitEvent(st, c->ev_fork, 0), "hipStreamWaitEvent");
       a.cls = ci;
       if (per_launch) HIP_OK(hipEventRecord(c->ev_cls0[ci], st), "hipEventRecord");
-      HIP_OK(hipLaunchKernel(c->plan[ci].kern, dim3(launch_grid(c, c->plan[ci], n)), dim3(256), args, 0, st),
+      const Cls& cl = c->plan[ci];
+      const bool split = use_split(c, cl, n);
+      const int grid = split ? launch_grid(c, 2 * cl.L, cl.split_grid, n) : launch_grid(c, cl.L, cl.grid, n);
+      HIP_OK(hipLaunchKernel(split ? cl.split : cl.kern, dim3(grid), dim3(256), args, 0, st),
              "persistent kernel launch");
       if (per_launch) {
         HIP_OK(hipEventRecord(c->ev_cls1[ci], st), "hipEventRecord");

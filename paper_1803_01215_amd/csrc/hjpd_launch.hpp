@@ -18,10 +18,16 @@ inline constexpr int kMaxCapacity = 256;
 // recipes, the eikonal family's weighted discretisations (forward Euler,
 // trapezoid), and the eikonal family's shifted-layout kernel for Algorithms 1
 // and 2 (which kVarPlain also selects for that family).
-enum Variant { kVarPlain = 0, kVarRecipe = 1, kVarMix = 2, kVarShift = 3, kVarShiftHopf = 4, kVarGameLax = 5 };
+enum Variant { kVarPlain = 0, kVarRecipe = 1, kVarMix = 2, kVarShift = 3, kVarShiftHopf = 4, kVarGameLax = 5, kVarSplit = 6 };
 
 template <typename T, class F, int L, int K>
 const void* group_ptr(int variant) {
+  if (variant == kVarSplit) {
+    // L lanes with one node each, in place of L/2 lanes with two (in FP64 the two
+    // compile to different roundings)
+    if constexpr (F::kSplit && sizeof(T) == 4 && K == 1 && L >= 32) return reinterpret_cast<const void*>(&k_group_control<T, F, L, K, false, 2>);
+    else return nullptr;
+  }
   if constexpr (F::kGame) {
     if constexpr (F::kGameHopf) {
       // scalar-player game: Algorithm 4 (kVarPlain) or Algorithm 3 (kVarGameLax) in one kernel
@@ -58,7 +64,8 @@ const void* group_ptr(int variant) {
 // the robustness recipes; the game kernel with the sigma and value-change
 // recipes), kVarMix (weighted Euler discretisations),
 // kVarShift / kVarShiftHopf (Algorithm 1 / 2 in the shifted layout, eikonal
-// family), kVarGameLax (Algorithm 3 for the scalar-player game).
+// family), kVarGameLax (Algorithm 3 for the scalar-player game), kVarSplit
+// (the quadrotor's split tiles).
 template <typename T, class F>
 const void* pick_kernel(int plain, int L, int K, int variant) {
   if (plain) {

@@ -65,3 +65,29 @@ def test_a_point_that_overflows_stops_alone(oracle_mod, name, tile):
     others = np.arange(w.n) != 5
     for k in ("iters", "status", "phi"):
         assert np.array_equal(g[k][others], base[k][others]), k
+
+
+@pytest.mark.parametrize("hopf", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [1, 61])
+@pytest.mark.parametrize("L,lo,hi", [(16, 17, 32), (32, 33, 64)])
+def test_split_tiles_give_the_same_bits(L, lo, hi, n, dtype, hopf):
+    """A small quadrotor batch runs tiles of 2L lanes with one node each in
+    place of L lanes with two (which a context asked for the tile keeps):
+    values, counts, statuses and both trajectories are the same bits, at both
+    ends of the class's N, for points that converge and points at the cap."""
+    w = W.quadrotor12().subset(np.arange(n))
+    w.N = np.random.default_rng(5).integers(lo, hi + 1, n).astype(np.int32)
+    w.N[0] = lo if n > 1 else hi
+    w.N[-1] = hi
+    w.t = 0.05 * w.N
+    w.N_max = hi
+    w.extra = dict(w.extra, ids=np.arange(n))
+    for cap, tol in ((3, 1e-6), (600, 1e-2), (600, 1e-30)):
+        a = gpu_solve(w, dtype=dtype, tol=tol, max_iter=cap, hopf=hopf)
+        b = gpu_solve(w, dtype=dtype, tol=tol, max_iter=cap, hopf=hopf, lanes_per_point=L, nodes_per_lane=2)
+        for k in ("iters", "status", "phi"):
+            assert np.array_equal(a[k], b[k], equal_nan=True), k
+        for i in range(n):
+            for k in ("x_traj", "p_traj"):
+                assert np.array_equal(a[k][i, :w.N[i] + 1], b[k][i, :w.N[i] + 1], equal_nan=True), (k, i)
