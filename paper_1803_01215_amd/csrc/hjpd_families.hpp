@@ -101,6 +101,11 @@ struct CNorm {
     C.gc1 = -P.alpha * s1 * s2;
   }
 
+  // c(x) = 1 everywhere: the eikonal equation proper, whose iteration needs no
+  // sine or cosine (speed() gives exactly 1 and zeros then).
+  template <typename T>
+  __device__ static bool constant_speed(const Par<T>& P) { return P.alpha == T(0); }
+
   // Speed c(x) = 1 + alpha sin(x_1) cos(x_2) and the two non-zero
   // components of its gradient.
   template <typename T>

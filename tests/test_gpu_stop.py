@@ -91,3 +91,25 @@ def test_split_tiles_give_the_same_bits(L, lo, hi, n, dtype, hopf):
         for i in range(n):
             for k in ("x_traj", "p_traj"):
                 assert np.array_equal(a[k][i, :w.N[i] + 1], b[k][i, :w.N[i] + 1], equal_nan=True), (k, i)
+
+
+@pytest.mark.parametrize("opt", [dict(), dict(hopf=True), dict(disc="fe"), dict(disc="trap")])
+@pytest.mark.parametrize("tile", [(8, 1), (16, 1), (8, 3), (64, 1), (16, 4)])
+def test_constant_speed_path_gives_the_same_bits(tile, opt):
+    """FP64 leaves the sines and cosines of the eikonal speed out where alpha
+    is 0 (of either sign).  With alpha = 1e-290 they are formed, but the speed
+    rounds to 1 and its gradient's terms vanish beside any step: the same bits."""
+    w = W.cnorm10(45)
+    w.N = np.random.default_rng(3).integers(1, 9, w.n).astype(np.int32)
+    w.N_max = 8
+    out = []
+    for alpha in (0.0, -0.0, 1e-290):
+        w.hp = np.array([alpha])
+        out.append(gpu_solve(w, dtype="f64", tol=1e-6, max_iter=300, lanes_per_point=tile[0], nodes_per_lane=tile[1],
+                             **opt))
+    for o in out[1:]:
+        for k in ("phi", "iters", "status"):
+            assert np.array_equal(out[0][k], o[k]), k
+        for i in range(w.n):
+            for k in ("x_traj", "p_traj"):
+                assert np.array_equal(out[0][k][i, :w.N[i] + 1], o[k][i, :w.N[i] + 1]), (k, i)
