@@ -24,12 +24,13 @@
 //   what the SIMD can), and with the rare block inside the loop every iteration
 //   carried its control flow and the register copies that joined its paths:
 //   about 14 % of the instructions of the isaacs tiles, 5-9 % of the others.
-//   Times with the rare block inside and, where noted, all residual sums formed
-//   in every iteration, against now: 4.00 -> 3.46 ms (256 points, d = 2, FP64),
-//   1,058 -> 864 us (2,051 points, d = 3, Hopf), 48.4 -> 39.6 ms (4,099 quadrotor
-//   points), 251 -> 227 ms (65,536 points of the pursuit game), 14.4 -> 10.3 ms
-//   (Isaacs' game).  Running the body twice per trip, which would save the
-//   copies of the costates that an iteration ends with, spilled instead.
+//   Times with the rare block inside and all residual sums formed in every
+//   iteration, against now: 4.01 -> 3.48 ms (256 points, d = 2, FP64), 532 -> 442
+//   us (2,051 points, d = 3, Hopf), 6.23 -> 5.69 ms (65,536 points, d = 10), 48.5 ->
+//   40.2 ms (4,099 quadrotor points), 252 -> 233 ms (65,536 points of the pursuit
+//   game), 14.2 -> 10.9 ms (Isaacs' game).  Running the body twice per
+//   trip, which would save the copies of the costates that an iteration ends
+//   with, spilled instead.  Exceptions stand at kInner.
 //
 // Plain kernel
 //   One point per lane, the whole stacked state of the point in a global
@@ -223,6 +224,10 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
   // the value has -g*(p_1) in place of g(x_0).  A uniform switch.
   const bool hopf = F::kHopfGroup && a.hopf;
   const T wl = a.wl, wr = a.wr;  // kW: H weights at an interval's left / right node
+  // The weighted rules and FP64 keep one iteration per trip of the outer loop:
+  // with what is constant over an inner loop taken out of it, they round
+  // differently, and this iteration amplifies that.
+  constexpr bool kInner = sizeof(T) == 4 && !kW;
 
   T x[K][D], p[K][D], z[K][D], x0[D], z0[D];
   T tj[K], tdj[K];  // per node: tau and tau*delta where the node takes a primal step, else 0
@@ -506,7 +511,7 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
         fin = M<T>::finite(rxs + rps);
         small = (rxs < a.tol) && (rps < a.tol);
       }
-    } while (!any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
+    } while (kInner && !any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     const bool done = active && (!fin || (!a.fixed && small) || k >= a.max_iter);
     if (done) {
       // value: Lagrangian at the last iterate (Algorithm 1)
@@ -938,13 +943,18 @@ __global__ void __launch_bounds__(256, (kShiftWaves<T, K>)) k_group_control_shif
   // node-0 prox as m v + f (first lane; identity elsewhere) when it is affine
   T m0, f0[D];
   const bool aff0 = F::prox0_affine(P, first, m0, f0);
+  // FP64 Hopf tiles of at most 16 lanes with two nodes of d = 10 have no register
+  // left for the inner loop's form: 16x2 on 65,536 points 12.8 ms with the rare
+  // block inside the loop and 14.4 with it outside (32x2: 14.1 and 13.3).  They
+  // keep it inside, and the sines and cosines too.
+  constexpr bool kInner = !(sizeof(T) == 8 && kHopf && L <= 16 && K * D >= 20);
   // With c(x) = 1 the sines and cosines, most of an FP64 iteration's
   // instructions in few dimensions, are left out: a wave-uniform branch, 3.52 ->
   // 1.33 ms for 256 points of d = 2 and 13.7 -> 4.45 ms for 20,000; d = 10 with
   // c not constant 9.1-9.2 ms without the branch, 8.4-9.3 with it.  In FP32,
   // where they are four instructions each, the branch costs the other case 3-6 %
   // and is not taken.
-  const bool still = sizeof(T) == 8 && F::constant_speed(P);
+  const bool still = sizeof(T) == 8 && kInner && F::constant_speed(P);
   const T mm0 = m0 - T(1);
   // Lazy p residual (below) keeps the previous dual live through the primal
   // step: K*D more registers, taken only where the register budget is modest
@@ -1116,7 +1126,7 @@ __global__ void __launch_bounds__(256, (kShiftWaves<T, K>)) k_group_control_shif
       }
       fin = M<T>::finite(rxs + rps);
       small = (rxs < a.tol) && (rps < tolp);
-    } while (!any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
+    } while (kInner && !any_lane(active && (!fin || (!a.fixed && small) || k >= k_next)));
     const bool done = active && (!fin || (!a.fixed && small) || k >= a.max_iter);
     if (done) {
       // value: g(x_0) + sum_j <p_j, x_j - x_{j-1}> - delta sum_j c(x_j) |p_j|,
