@@ -394,13 +394,13 @@ def bench_c5(B, steps, cpu):
             "forward_kernel_ms": fwd_ms, "forward_solves_per_s": w.n / (fwd_ms * 1e-3),
             "roofline": {"bound": "mfma", "achieved": flops / (fwd_ms * 1e-3) / 1e12, "peak": PEAK["fp32_matrix"] / 1e12,
                          "unit": "TFLOP/s", "frac": flops / (fwd_ms * 1e-3) / PEAK["fp32_matrix"],
-                         "kernel": "k_lt_forward<100>", "flops_per_launch": flops, "traffic": None},
+                         "kernel": "k_lt_forward<100, 4>", "flops_per_launch": flops, "traffic": None},
             "value_grad_ms": vg_ms, "value_grad_points_per_s": w.n / (vg_ms * 1e-3), "ckpt_every": 50,
             "backward_kernel_ms": bwd_ms,
             "backward_roofline": {"bound": "mfma", "achieved": bflops / (bwd_ms * 1e-3) / 1e12,
                                   "peak": PEAK["fp32_matrix"] / 1e12, "unit": "TFLOP/s",
                                   "frac": bflops / (bwd_ms * 1e-3) / PEAK["fp32_matrix"],
-                                  "kernel": "k_lt_backward<100>", "flops_per_launch": bflops, "traffic": None},
+                                  "kernel": "k_lt_backward<100, 4>", "flops_per_launch": bflops, "traffic": None},
             "cpu_baseline": oracle_sample(w, 256) if cpu else None}
 
 
