@@ -1,8 +1,9 @@
 """Build libhjpd.so for gfx950 with hipcc (in-tree).
 
 Translation units are compiled in parallel: the C-ABI layer, the
-linear-tanh unit and one kernel-instantiation unit per (family shape,
-dtype).  All device code is compiled with packed FP32 instructions disabled.
+linear-tanh unit and the kernel-instantiation units, one or two per (family
+shape, dtype).  All device code is compiled with packed FP32 instructions disabled,
+and the linked library is kept only if isa_check finds nothing in it.
 """
 from __future__ import annotations
 
@@ -11,6 +12,11 @@ import os
 import shutil
 import subprocess
 import sys
+
+if __package__:
+    from . import isa_check
+else:  # run as a script
+    import isa_check
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -33,6 +39,22 @@ INSTANCES = [
     ("isaacs_f32", "Isaacs", "float"), ("isaacs_f64", "Isaacs", "double"),
 ]
 
+# The FP64 four-node tiles of the two widest families are units of their own,
+# compiled with the constants of the sine and cosine left beside their uses
+# instead of moved out of the iteration: those registers are short, and with the
+# constants moved out the allocator misplaced register copies in three of these
+# kernels (isa_check.py).  Same arithmetic and bits.  Against the tiles compiled
+# as the rest: quadrotor 8x4 2.25 -> 2.03 ms and 64x4 5.3 -> 3.75 ms (2,000
+# points, 150 iterations; before the misplaced copies came in), d = 10 16x4 1.97
+# -> 2.03 ms (10,007 points, 200 iterations); for the narrower tiles it costs up
+# to 3 %.
+K4_FLAGS = ["-DHJPD_K_LO=4", "-mllvm", "-disable-machine-licm"]
+UNIT_FLAGS = {}
+for _name, _fam, _real in [i for i in INSTANCES if i[0] in ("quad_f64", "cnorm10_f64")]:
+    INSTANCES.append((_name + "_k4", _fam, _real))
+    UNIT_FLAGS[_name] = ["-DHJPD_K_HI=3", "-DHJPD_K4=%s_k4" % _name]
+    UNIT_FLAGS[_name + "_k4"] = K4_FLAGS
+
 
 def _run(cmd):
     p = subprocess.run(cmd, capture_output=True, text=True)
@@ -50,7 +72,7 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
     cmds, objs = [], []
     for name, fam, real in INSTANCES:
         o = os.path.join(BUILD, "inst_%s.o" % name)
-        cmds.append([HIPCC, *FLAGS, "-DHJPD_FAM=%s" % fam, "-DHJPD_REAL=%s" % real, "-DHJPD_NAME=%s" % name,
+        cmds.append([HIPCC, *FLAGS, *UNIT_FLAGS.get(name, []), "-DHJPD_FAM=%s" % fam, "-DHJPD_REAL=%s" % real, "-DHJPD_NAME=%s" % name,
                      "-c", os.path.join(CSRC, "hjpd_inst.hip"), "-o", o])
         objs.append(o)
     for unit in ("hjpd_api", "hjpd_lintanh", "hjpd_calib"):
@@ -64,6 +86,10 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
                 print(msg, file=sys.stderr)
     tmp = LIB + ".tmp%d" % os.getpid()
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
+    bad = isa_check.misplaced(tmp, HIPCC, jobs)
+    if bad:
+        os.remove(tmp)
+        raise RuntimeError("kernels with register copies before an EXEC restore (isa_check.py): %s" % ", ".join(sorted(bad)))
     os.replace(tmp, LIB)
     return LIB
 

@@ -3,6 +3,14 @@
 
 #include "hjpd_kernels.hpp"
 
+// Nodes per lane of the tiles that this unit instantiates.
+#ifndef HJPD_K_LO
+#define HJPD_K_LO 1
+#endif
+#ifndef HJPD_K_HI
+#define HJPD_K_HI 4
+#endif
+
 namespace hjpd {
 
 // Persistent tiles (lanes per point L, nodes per lane K) that are compiled.
@@ -69,15 +77,18 @@ const void* group_ptr(int variant) {
 template <typename T, class F>
 const void* pick_kernel(int plain, int L, int K, int variant) {
   if (plain) {
-    if constexpr (F::kGame) {
+    if constexpr (HJPD_K_LO > 1) {
+      return nullptr;  // in the unit of the other tiles
+    } else if constexpr (F::kGame) {
       if constexpr (F::kGameHopf) return nullptr;  // no plain kernel for the game Hopf formulation
       else return reinterpret_cast<const void*>(&k_plain_game<T, F>);
     } else {
       return reinterpret_cast<const void*>(&k_plain_control<T, F>);
     }
   }
-#define HJPD_TILE_CASE(LL, KK) \
-  if (L == LL && K == KK) return group_ptr<T, F, LL, KK>(variant);
+#define HJPD_TILE_CASE(LL, KK)                                          \
+  if constexpr (KK >= HJPD_K_LO && KK <= HJPD_K_HI)                   \
+    if (L == LL && K == KK) return group_ptr<T, F, LL, KK>(variant);
   HJPD_TILE_CASE(8, 1) HJPD_TILE_CASE(16, 1) HJPD_TILE_CASE(8, 2) HJPD_TILE_CASE(8, 3) HJPD_TILE_CASE(32, 1) HJPD_TILE_CASE(16, 2)
   HJPD_TILE_CASE(8, 4) HJPD_TILE_CASE(16, 3) HJPD_TILE_CASE(64, 1) HJPD_TILE_CASE(32, 2) HJPD_TILE_CASE(16, 4) HJPD_TILE_CASE(32, 3)
   HJPD_TILE_CASE(64, 2) HJPD_TILE_CASE(32, 4) HJPD_TILE_CASE(64, 3) HJPD_TILE_CASE(64, 4)
