@@ -328,6 +328,10 @@ int hjpd_set_pop_counter(hjpd_ctx *ctx, int32_t *counts);
  * min(hi[c], N_max), 1..16 classes, tiles among the compiled ones (L in {8,
  * 16, 32, 64}, K in 1..4; capacities 8, 16, 24, 32, 48, 64, 96, 128, 192,
  * 256).  EINVAL / EUNSUPPORTED otherwise, with the previous plan kept.
+ * The plan's tiles are the ones that run, at every batch size.  (Only the
+ * default partition of a new context may run an FP32 quadrotor class of 16x2 or
+ * 32x2 on twice the lanes with one node each while the batch is small; results
+ * are the same bits, and hjpd_get_launch_timing names the tile that ran.)
  * A point's result depends on the tile that serves it (its lanes and nodes
  * per lane fix the summation order of its residuals, so a stop decision can
  * differ in the last bit) but not on the class boundaries, the other points
@@ -360,8 +364,8 @@ int hjpd_get_timing(hjpd_ctx *ctx, double *ms, int *launches);
  * completed solve, measured with HIP events on the stream that launch ran on
  * (each capacity class is one persistent launch, section 7's per-point
  * independence lets the classes run side by side), and the launch's class:
- * the N range [*N_lo, *N_hi] it served and its tile (lanes per point, nodes
- * per lane).  Output pointers other than ms may be NULL.  Synchronises on
+ * the N range [*N_lo, *N_hi] it served and the tile that ran (lanes per point,
+ * nodes per lane).  Output pointers other than ms may be NULL.  Synchronises on
  * the launch's end event.  EINVAL if timing is off, no such solve has run,
  * or i is out of range.
  */

@@ -227,8 +227,13 @@ struct Cls {
   int lo, hi, L, K;
   const void* kern;
   int grid;  // persistent grid (blocks of 256)
-  const void* split = nullptr;  // the same sums on twice the lanes, one node each (small batches), or null
+  const void* split = nullptr;  // default partition: the same sums on twice the lanes, one node each (small batches), or null
   int split_grid = 0;
+};
+
+// One timed persistent launch: the class and the tile that ran (the class's, or its split tile).
+struct TimedLaunch {
+  int cls, lo, hi, L, K;
 };
 
 // Device scratch of one solve: the bucket counters and cursors, the class
@@ -289,10 +294,11 @@ struct hjpd_ctx {
   int timing_launches = 0;
   // per persistent launch (one per capacity class), recorded on the launch's own stream
   std::vector<hipEvent_t> ev_cls0, ev_cls1;
-  std::vector<int> timed_cls;  // class index of each timed launch, in launch order
+  std::vector<TimedLaunch> timed;  // in launch order
   // linear-tanh (differentiation) state
   hjpd::LtState* lt = nullptr;
   bool plan_from_cache = false;  // the plan came from the on-disk tuning cache
+  bool plan_default = false;     // the plan is the default partition
   int32_t* d_pops = nullptr;     // caller's pop counter (hjpd_set_pop_counter), not owned
 };
 
@@ -380,9 +386,10 @@ int launch_grid(const hjpd_ctx* c, int L, int full, int64_t n) {
   return int(grid);
 }
 
-// Whether a class runs its split tile (twice the lanes per point, one node
-// each, the same results): while the whole batch in it makes at most
-// kSplitWavesPerCU waves per CU.  Fewer points end sooner, since the slowest
+// Whether a class of the default partition runs its split tile (twice the lanes
+// per point, one node each, the same results): while the whole batch in it
+// makes at most kSplitWavesPerCU waves per CU.  A plan that was asked for (by
+// the descriptor, hjpd_set_plan, the tuner or its cache) runs the tiles it names.  Fewer points end sooner, since the slowest
 // ones take 1.6 times less time an iteration; more of them fill the SIMDs, and
 // then two nodes per lane, which share a point's exchanges and tests, win.
 // Quadrotor, N up to 60, two nodes against split: 25.7 / 16.8 ms (64 points),
@@ -400,8 +407,9 @@ int ensure_class_events(hjpd_ctx* c);
 // Install a class partition: validate it, look up the kernels, upload the
 // class bounds, and make sure there are side streams for the parallel
 // branches and (with HJPD_TIMING) per-launch events.  The last class's hi is
-// clamped to N_max; classes past N_max are dropped.
-int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec) {
+// clamped to N_max; classes past N_max are dropped.  is_default: the default
+// partition, whose two-node classes may run as split tiles.
+int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec, bool is_default = false) {
   const hjpd_desc& D = c->desc;
   Lookup lk = lookup_for(D);
   if (!lk) return fail(HJPD_EUNSUPPORTED, "no persistent kernels for this family");
@@ -418,8 +426,7 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec) {
     cl.kern = lk(0, cs.L, cs.K, kernel_variant(D));
     if (!cl.kern) return fail(HJPD_EUNSUPPORTED, "plan: tile not built");
     cl.grid = persistent_grid(c, cl.kern);
-    // a tile asked for by the descriptor is the one that runs
-    if (cs.K == 2 && (cs.L == 16 || cs.L == 32) && kernel_variant(D) == hjpd::kVarPlain && D.lanes_per_point == 0)
+    if (is_default && cs.K == 2 && (cs.L == 16 || cs.L == 32) && kernel_variant(D) == hjpd::kVarPlain)
       cl.split = lk(0, 2 * cs.L, 1, hjpd::kVarSplit);
     if (cl.split) cl.split_grid = persistent_grid(c, cl.split);
     plan.push_back(cl);
@@ -458,6 +465,7 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec) {
   }
   drop_graph(c);
   c->plan = plan;
+  c->plan_default = is_default;
   if (D.flags & HJPD_TIMING) return ensure_class_events(c);
   return HJPD_OK;
 }
@@ -540,7 +548,7 @@ int build_plan(hjpd_ctx* c, bool* from_cache) {
     }
     g_err.clear();  // an unusable cache entry falls back to the default
   }
-  int rc = apply_spec(c, default_spec(c->desc.N_max));
+  int rc = apply_spec(c, default_spec(c->desc.N_max), true);
   c->plain_kern = lookup_for(c->desc)(1, 0, 0, 0);
   return rc;
 }
@@ -713,7 +721,7 @@ int enqueue_solve(hjpd_ctx* c, const Workspace& ws, int64_t n, const void* x, co
     const int nside = std::min(ncls - 1, kMaxBranches - 1);
     const bool fork = nside > 0 && int(c->side.size()) >= nside;
     const bool per_launch = timed && int(c->ev_cls0.size()) >= ncls;
-    if (per_launch) c->timed_cls.clear();
+    if (per_launch) c->timed.clear();
     if (fork) HIP_OK(hipEventRecord(c->ev_fork, s), "hipEventRecord");
     for (int ci = ncls - 1; ci >= 0; ci--) {
       const int rank = ncls - 1 - ci;  // 0: the class of largest N
@@ -728,7 +736,7 @@ int enqueue_solve(hjpd_ctx* c, const Workspace& ws, int64_t n, const void* x, co
              "persistent kernel launch");
       if (per_launch) {
         HIP_OK(hipEventRecord(c->ev_cls1[ci], st), "hipEventRecord");
-        c->timed_cls.push_back(ci);
+        c->timed.push_back({ci, cl.lo, cl.hi, split ? 2 * cl.L : cl.L, split ? 1 : cl.K});
       }
       if (st != s) HIP_OK(hipEventRecord(c->ev_join[rank], st), "hipEventRecord");
       launches++;
@@ -1008,16 +1016,16 @@ int hjpd_get_launch_timing(hjpd_ctx* c, int i, double* ms, int* N_lo, int* N_hi,
   if (!(c->desc.flags & HJPD_TIMING) || !c->timing_valid) return fail(HJPD_EINVAL, "no timed solve recorded");
   if (c->lt || (c->desc.flags & (HJPD_PLAIN | HJPD_GRAPH)))
     return fail(HJPD_EINVAL, "per-launch timing is recorded for eager persistent solves only");
-  if (i < 0 || i >= int(c->timed_cls.size())) return fail(HJPD_EINVAL, "launch index out of range");
-  const int ci = c->timed_cls[i];
-  HIP_OK(hipEventSynchronize(c->ev_cls1[ci]), "hipEventSynchronize");
+  if (i < 0 || i >= int(c->timed.size())) return fail(HJPD_EINVAL, "launch index out of range");
+  const TimedLaunch& t = c->timed[i];
+  HIP_OK(hipEventSynchronize(c->ev_cls1[t.cls]), "hipEventSynchronize");
   float f = 0;
-  HIP_OK(hipEventElapsedTime(&f, c->ev_cls0[ci], c->ev_cls1[ci]), "hipEventElapsedTime");
+  HIP_OK(hipEventElapsedTime(&f, c->ev_cls0[t.cls], c->ev_cls1[t.cls]), "hipEventElapsedTime");
   *ms = f;
-  if (N_lo) *N_lo = c->plan[ci].lo;
-  if (N_hi) *N_hi = c->plan[ci].hi;
-  if (lanes_per_point) *lanes_per_point = c->plan[ci].L;
-  if (nodes_per_lane) *nodes_per_lane = c->plan[ci].K;
+  if (N_lo) *N_lo = t.lo;
+  if (N_hi) *N_hi = t.hi;
+  if (lanes_per_point) *lanes_per_point = t.L;
+  if (nodes_per_lane) *nodes_per_lane = t.K;
   return HJPD_OK;
 }
 
@@ -1038,10 +1046,11 @@ int hjpd_set_plan(hjpd_ctx* c, int n_classes, const int32_t* hi, const int32_t* 
   std::vector<ClassSpec> v;
   for (int i = 0; i < n_classes; i++) v.push_back({hi[i], L[i], K[i]});
   const std::vector<ClassSpec> old = current_spec(c);
+  const bool old_default = c->plan_default;
   int rc = apply_spec(c, v);
   if (rc) {
     const std::string msg = g_err;
-    (void)apply_spec(c, old);
+    (void)apply_spec(c, old, old_default);
     return fail(rc, msg);
   }
   c->plan_from_cache = false;
@@ -1079,6 +1088,7 @@ int hjpd_autotune(hjpd_ctx* c, int64_t n, const void* x, const void* t, const in
   if (rc) return rc;
   const hjpd_desc saved = c->desc;
   const std::vector<ClassSpec> start_spec = current_spec(c);
+  const bool start_default = c->plan_default;
   // probes: exactly probe_iters iterations at every point, timed from the
   // first class launch to the last one's end on the caller's stream
   c->desc.flags = (saved.flags | HJPD_FIXED_ITERS | HJPD_TIMING) & ~unsigned(HJPD_GRAPH | HJPD_PLAIN);
@@ -1181,7 +1191,7 @@ int hjpd_autotune(hjpd_ctx* c, int64_t n, const void* x, const void* t, const in
   c->desc = saved;
   if (rc) {
     const std::string msg = g_err;
-    (void)apply_spec(c, start_spec);
+    (void)apply_spec(c, start_spec, start_default);
     return fail(rc, msg);
   }
   rc = apply_spec(c, spec);
