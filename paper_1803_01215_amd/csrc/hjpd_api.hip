@@ -299,6 +299,7 @@ struct hjpd_ctx {
   hjpd::LtState* lt = nullptr;
   bool plan_from_cache = false;  // the plan came from the on-disk tuning cache
   bool plan_default = false;     // the plan is the default partition
+  int split_lanes = 0;           // lanes per point of its widest split tile
   int32_t* d_pops = nullptr;     // caller's pop counter (hjpd_set_pop_counter), not owned
 };
 
@@ -387,18 +388,23 @@ int launch_grid(const hjpd_ctx* c, int L, int full, int64_t n) {
 }
 
 // Whether a class of the default partition runs its split tile (twice the lanes
-// per point, one node each, the same results): while the whole batch in it
-// makes at most kSplitWavesPerCU waves per CU.  A plan that was asked for (by
-// the descriptor, hjpd_set_plan, the tuner or its cache) runs the tiles it names.  Fewer points end sooner, since the slowest
+// per point, one node each, the same results): while the whole batch on the
+// partition's widest split tile makes at most kSplitWavesPerCU waves per CU.  A
+// plan that was asked for (by the descriptor, hjpd_set_plan, the tuner or its
+// cache) runs the tiles it names.  Fewer points end sooner, since the slowest
 // ones take 1.6 times less time an iteration; more of them fill the SIMDs, and
-// then two nodes per lane, which share a point's exchanges and tests, win.
-// Quadrotor, N up to 60, two nodes against split: 25.7 / 16.8 ms (64 points),
-// 26.4 / 17.0 (500), 39.5 / 32.0 (3,000 points, 12 waves per CU of 64 lanes),
-// 39.7 / 39.1 (4,099; in another batch of that size 40.2 / 43.5), 39.9 / 41.3
-// (4,600), 45.0 / 49.5 (6,000), 97.1 / 105.7 (16,384).
+// then two nodes per lane, which share a point's exchanges and tests, win.  The
+// classes run side by side, so one does not split alone while a wider one ends
+// the batch: it would only take issue slots from that.
+// Quadrotor, two nodes against split, ms.  N from 11 to 60 (both classes):
+// 26.5 / 17.3 (200 points), 39.3 / 29.4 (2,500), 39.5 / 29.5 (3,000; 3,072 is the
+// line); with the 16x2 class split alone 39.7 / 39.7 (3,600), 39.8 / 44.3 (4,800),
+// 40.8 / 45.7 (5,400).  N from 17 to 32 (16x2 alone): 17.8 / 12.1 (200), 24.6 / 19.6
+// (4,200), 25.7 / 18.8 (6,100; 6,144 is the line).  N from 34 to 60 (32x2 alone):
+// 26.8 / 17.3 (200), 39.9 / 40.1 (2,500), 40.0 / 38.5 (3,000).
 constexpr int kSplitWavesPerCU = 12;
 bool use_split(const hjpd_ctx* c, const Cls& cl, int64_t n) {
-  return cl.split && n * (2 * cl.L) <= int64_t(64) * kSplitWavesPerCU * c->n_cu;
+  return cl.split && n * c->split_lanes <= int64_t(64) * kSplitWavesPerCU * c->n_cu;
 }
 
 void drop_graph(hjpd_ctx* c);
@@ -414,7 +420,7 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec, bool is_default 
   Lookup lk = lookup_for(D);
   if (!lk) return fail(HJPD_EUNSUPPORTED, "no persistent kernels for this family");
   std::vector<Cls> plan;
-  int prev = 0;
+  int prev = 0, split_lanes = 0;
   for (const ClassSpec& cs : spec) {
     if (cs.hi <= prev) return fail(HJPD_EINVAL, "plan: class bounds must ascend");
     if (cs.L * cs.K < std::min(cs.hi, D.N_max)) return fail(HJPD_EINVAL, "plan: a tile's capacity L*K is below its class's N");
@@ -428,7 +434,10 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec, bool is_default 
     cl.grid = persistent_grid(c, cl.kern);
     if (is_default && cs.K == 2 && (cs.L == 16 || cs.L == 32) && kernel_variant(D) == hjpd::kVarPlain)
       cl.split = lk(0, 2 * cs.L, 1, hjpd::kVarSplit);
-    if (cl.split) cl.split_grid = persistent_grid(c, cl.split);
+    if (cl.split) {
+      cl.split_grid = persistent_grid(c, cl.split);
+      split_lanes = 2 * cs.L;  // (wider with every class)
+    }
     plan.push_back(cl);
     prev = cl.hi;
     if (prev >= D.N_max) break;
@@ -466,6 +475,7 @@ int apply_spec(hjpd_ctx* c, const std::vector<ClassSpec>& spec, bool is_default 
   drop_graph(c);
   c->plan = plan;
   c->plan_default = is_default;
+  c->split_lanes = split_lanes;
   if (D.flags & HJPD_TIMING) return ensure_class_events(c);
   return HJPD_OK;
 }
