@@ -15,6 +15,12 @@
 //        vbar = c1 PB;  Ppre = vbar;  Zpre_j = sigma (vbar_j - vbar_{j+1})
 //        Xpre_j += lam (A^T vbar)_j + lam eps (1 - th_j^2) vbar_j;  dA += lam vbar_j x_j^T;  deps += lam th vbar
 //
+// x_N does not move, so its adjoint, most of dphi/dx, only ever grows, by terms
+// far smaller than itself.  At node N those terms are gathered in the z adjoint
+// first (which the next step adds to the x adjoint whole), so each step rounds
+// once at the size of the sum: dphi/dx is 2.7e-7 (rms) from 64 bits after 100
+// iterations at d = 32, where adding the terms one by one left 5.7e-7.
+//
 // XB and ZB stay in registers.  d > 32: a step has two barriers.  Between them
 // the waves read the images of XB and of their own rows of -tau delta p' (A XB,
 // the outer product p' XB^T) and write those of vbar and lam x; after the
@@ -269,7 +275,8 @@ struct LtBack : LtCore<D, NT, KIND, true> {
     int np = __builtin_amdgcn_readfirstlane(Np);
     asm volatile("" : "+s"(np));
     const int n0 = this->node_now();
-    // (A) extrapolation transposed: XB_j (zero at j = N, where x is fixed) and Zpre
+    // (A) extrapolation transposed: XB_j (zero at j = N, where x is fixed), and
+    // Xpre_j's XB_j - theta ZB_j = x' + z' in one rounding
     asm volatile("" ::"v"(touched));
     if constexpr (kRows)
 #pragma unroll
@@ -281,7 +288,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
           for (int r = 0; r < 4; r++) {
             const float xb = ZB[ri][t][r], zb = XB[ri][t][r];
             XB[ri][t][r] = mid ? xb + (1.f + theta) * zb : 0.f;
-            ZB[ri][t][r] = mid ? -theta * zb : zb + xb;
+            ZB[ri][t][r] = xb + zb;
           }
           if constexpr (S::kReg) scratch_put(1, ri, t, XB[ri][t]);
           else this->put(this->imgX, this->tailX, t, XB[ri][t]);
@@ -327,10 +334,12 @@ struct LtBack : LtCore<D, NT, KIND, true> {
       wb[0] = this->first_col(ld4(this->sWb + this->coord_now()));
     }
     if constexpr (kRows) {
-      f4 xbm[RPW], vfirst[RPW], vlast[RPW];
+      f4 xbm[RPW], vfirst[RPW], vlast[RPW], end[RPW];
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++) xbm[ri] = row_prev(XB[ri][NT - 1]) + wb[ri];
       this->sweep(fr, this->imgX, this->tailX, XB, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
+        const bool last = n0 + t == np;
+        const float le = last ? 0.f : lam * eps, le_end = last ? lam * eps : 0.f;
 #pragma unroll
         for (int ri = 0; ri < RPW; ri++) {
           const f4 xk = xn[ri], pt = pn[ri];
@@ -341,21 +350,23 @@ struct LtBack : LtCore<D, NT, KIND, true> {
           f4 pb;
           if constexpr (S::kPbLds) pb = ld4(at<true>(this->sPb, 4 * tid) + 256 * RT * t);
           else pb = PB[ri][t];
-          f4 vb;
+          f4 vb, ve;
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const float xb = XB[ri][t][r], pp = pt[r], th = tanh_fast(xk[r]);
             const float om = 1.f - th * th, q = om * xb, s = pp * q;
             const float v = (pb[r] + (tau * (xbm[ri][r] - xb) - td * (acc[ri][r] + eps * q))) * c1;
             vb[r] = v;
-            ZB[ri][t][r] += xb + (2.f * td * eps) * (th * s) + (lam * eps) * (om * v);
+            ZB[ri][t][r] += (2.f * td * eps) * (th * s) + le * (om * v);
+            ve[r] = le_end * (om * v);
             s1 += s;
             s2 += th * v;
           }
           xbm[ri] = XB[ri][t];
-          if (t > 0) XB[ri][t > 0 ? t - 1 : 0] = sigma * (vlast[ri] - vb);
+          if (t > 0) XB[ri][t > 0 ? t - 1 : 0] = sigma * (vlast[ri] - vb) + end[ri];
           else vfirst[ri] = vb;
           vlast[ri] = vb;
+          end[ri] = ve;
           if constexpr (S::kPbLds) st4(at<true>(this->sPb, 4 * tid) + 256 * RT * t, vb);
           else PB[ri][t] = vb;
           if constexpr (S::kReg) {
@@ -369,7 +380,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
       });
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++) {
-        XB[ri][NT - 1] = sigma * (vlast[ri] - row_next(vfirst[ri]));
+        XB[ri][NT - 1] = sigma * (vlast[ri] - row_next(vfirst[ri])) + end[ri];
         if constexpr (S::kReg) {
 #pragma unroll
           for (int r = 0; r < 4; r++) zb0[ri][r] = lr == 0 ? -sigma * vfirst[ri][r] : 0.f;
@@ -404,8 +415,13 @@ struct LtBack : LtCore<D, NT, KIND, true> {
       else outer(this->imgP, this->img3);
       this->fence();
       this->sweep(fr, this->imgP, this->tailP, PB, [&](int t, const f4(&acc)[RPW]) __attribute__((always_inline)) {
+        const bool last = n0 + t == np;
+        const float la = last ? 0.f : lam, la_end = last ? lam : 0.f;
 #pragma unroll
-        for (int ri = 0; ri < RPW; ri++) ZB[ri][t] += lam * acc[ri];
+        for (int ri = 0; ri < RPW; ri++) {
+          ZB[ri][t] += la * acc[ri];
+          XB[ri][t] += la_end * acc[ri];
+        }
       });
     }
   }

@@ -333,3 +333,39 @@ def test_column_tile_edges_gradients(oracle_mod, d, N_max):
     assert bar(g["dh"][:1], de.reshape(1)) <= 1e-4
     assert bar(g["dh"][1:], dA) <= 1e-4
     assert bar(g["dg"], dQ) <= 1e-4
+
+
+def _reference_gradients(O, w, K, wts):
+    """(phi, d/dx, d/deps, d/dA, d/dQ) in binary64 by autograd through the unrolled iterations, on the
+    inputs as the GPU gets them."""
+    import torch
+    n, d = w.n, w.d
+    noise = [np.zeros((n, w.N_max + 1, d)) for _ in range(2)]
+    for i in range(n):
+        for j in range(w.N_max + 1):
+            for c in range(d):
+                noise[0][i, j, c] = O.init_noise(w.init_seed, i, 0, j, c)
+                noise[1][i, j, c] = O.init_noise(w.init_seed, i, 1, j, c)
+    T = lambda a: torch.tensor(a, dtype=torch.float64)
+    x, A, Q = T(_f32(w.x)).requires_grad_(), T(_f32(w.hp[1:])).reshape(d, d).requires_grad_(), \
+        T(_f32(w.gp)).reshape(d, d).requires_grad_()
+    eps = T(_f32(w.hp[0])).requires_grad_()
+    phi = _torch_phi(x, T(_f32(w.t)), w.N, eps, A, Q, T(noise[0]), T(noise[1]), K, float(w.sigma), float(w.tau))
+    g = torch.autograd.grad((phi * T(_f32(wts))).sum(), [x, eps, A, Q])
+    return (phi.detach().numpy(),) + tuple(v.numpy() for v in g)
+
+
+@pytest.mark.parametrize("d", [16, 32, 100, 128])
+def test_rounding_of_the_query_point_gradient(oracle_mod, d):
+    """dphi/dx gathers small terms over every iteration on a sum far larger
+    than they are.  A float32 model of the sweep (N = 24, 100 iterations) is
+    2.6e-7 to 2.7e-7 from binary64 in the root mean square where a step rounds
+    once at the sum's size, and 5.6e-7 to 5.9e-7 where it adds the terms one by
+    one; the bound lies between."""
+    w = _small_workload(d=d, n=8, N=24, K=100, seed=40 + d)
+    wts = np.random.default_rng(d).uniform(0.5, 1.5, w.n)
+    g = _gpu_lt(w, 100, 25, wts)
+    want = _reference_gradients(oracle_mod, w, 100, wts)[1]
+    err = np.linalg.norm(g["dx"] - want) / np.linalg.norm(want)
+    print("d = %d: rms error of dphi/dx %.3g" % (d, err))
+    assert err <= 4e-7
