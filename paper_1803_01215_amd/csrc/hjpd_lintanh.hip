@@ -190,11 +190,25 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
   float* seg = b.seg + int64_t(blockIdx.x) * (int64_t(E) * (2 * TF + 2 * D) + 2 * TF);
   float* adj = seg + int64_t(E) * 2 * TF;
   float* stage = adj + 2 * TF;  // per step of a segment: XB_0 and w = x_0 + tau p'_1
-  // dA is summed in registers; the direct dQ term and (d > 32) dM in this
-  // workgroup's partial block
+  // dA is summed in registers (with many column tiles, C::kFlush steps at a
+  // time); the direct dQ term and (d > 32) dM in this workgroup's partial block
   float* part = b.part + int64_t(blockIdx.x) * (3 * DD + 1);
-  for (int e = tid; e < DD; e += S::kThreads) part[DD + e] = part[2 * DD + e] = 0.f;
+  for (int e = tid; e < DD; e += S::kThreads) part[e] = part[DD + e] = part[2 * DD + e] = 0.f;
   __syncthreads();
+
+  // dA into the partial block (every entry has one lane that adds to it)
+  auto flush_dA = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ri = 0; ri < RPW; ri++)
+#pragma unroll
+      for (int ct = 0; ct < RT; ct++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int row = c.coord(ri) + r, col = 16 * ct + lr;
+          if (row < D && col < D) part[row * D + col] += c.dA[ri][ct][r];
+          c.dA[ri][ct][r] = 0.f;
+        }
+  };
 
   // Points are dealt to the workgroups in a fixed order (every point costs
   // the same K iterations), so each workgroup's partial sums of dA, dM, dQ and
@@ -340,9 +354,12 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
       float touched = 0.f;
       typename C::Tiles pk;
       if constexpr (C::kRows) c.load_tiles(seg + int64_t(nk - 1) * 2 * TF + TF, pk);
-      for (int k = nk - 1; k >= 0; k--) {
-        float* cur = seg + int64_t(k) * 2 * TF;
-        c.step(a, eps, stage + int64_t(k) * 2 * D, cur, k > 0 ? cur - 2 * TF : nullptr, pk, touched, xb0, zb0, s1, s2);
+      for (int k1 = nk; k1 > 0; k1 -= C::kFlush) {
+        for (int k = k1 - 1; k >= max(k1 - C::kFlush, 0); k--) {
+          float* cur = seg + int64_t(k) * 2 * TF;
+          c.step(a, eps, stage + int64_t(k) * 2 * D, cur, k > 0 ? cur - 2 * TF : nullptr, pk, touched, xb0, zb0, s1, s2);
+        }
+        if constexpr (C::kRows && C::kFlush < 1 << 30) flush_dA();
       }
       // dM += sum over the segment's steps of XB_0 w^T, in FP32 from the kept pairs
       if constexpr (S::kReg) {
@@ -420,19 +437,15 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
     __syncthreads();
   }
   // ---- per-workgroup partial parameter gradients ----------------------------------------
-  if constexpr (C::kRows)
+  if constexpr (C::kRows) flush_dA();
+  if constexpr (S::kReg)
 #pragma unroll
     for (int ri = 0; ri < RPW; ri++)
 #pragma unroll
       for (int ct = 0; ct < RT; ct++)
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int row = c.coord(ri) + r, col = 16 * ct + lr;
-          if (row < D && col < D) {
-            part[row * D + col] = c.dA[ri][ct][r];
-            if constexpr (S::kReg) part[DD + row * D + col] = c.dM[ri][ct][r];
-          }
-        }
+        for (int r = 0; r < 4; r++)
+          part[DD + (c.coord(ri) + r) * D + 16 * ct + lr] = c.dM[ri][ct][r];
   float zero = 0.f;
   c.sum2(c.deps, zero);
   if (tid == 0) part[3 * DD] = c.deps;

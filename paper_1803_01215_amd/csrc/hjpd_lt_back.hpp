@@ -133,7 +133,17 @@ struct LtBack : LtCore<D, NT, KIND, true> {
         o.q[c] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sh4*)(q.c + off + c * S::PIECE));
     }
   }
-  // dA += (this wave's rows of U) (all columns of V)^T
+  // dA += (this wave's rows of U) (all columns of V)^T, by six piece products.
+  // Added straight to dA, each of them rounds at dA's size, and not evenly: over
+  // all steps and points that left dA up to 3.4 times further from 64 bits than
+  // FP32 products do.  With up to two column tiles the six are summed apart;
+  // with more there are no registers for that (42 % slower at N = 50), and dA is
+  // added to the partial sums in memory and cleared every kFlush steps.
+  // rms error of dA at d = 100 with FP32 products, straight, and so: 9.0e-7, 2.4e-6,
+  // 1.8e-7 (1,442 points, N 19 to 25, 90 iterations); 1.4e-6, 4.6e-6, 5e-7 (700
+  // points, N = 50, 100 iterations).
+  static constexpr bool kApart = NT <= 2;
+  static constexpr int kFlush = S::kReg || kApart ? 1 << 30 : 16;
   __device__ __forceinline__ void outer(const lds_u16* U, const lds_u16* V) {
     // this wave's rows: its own row tile
     const At au = at_of(U + 2 * wave * S::ROWS * 8), av = at_of(V);
@@ -148,7 +158,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
         Op next;  // the next tile's reads, under this tile's products
         if (ct + 1 < RT) read_op(next, av, ct + 1, s);
         this->fence();
-        f4 v = dA[0][ct];
+        f4 v = kApart ? f4{0.f, 0.f, 0.f, 0.f} : dA[0][ct];
         // piece pairs (a, b), small products first
         constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -156,7 +166,8 @@ struct LtBack : LtCore<D, NT, KIND, true> {
           if (s < KS) v = mfma32(a.p[pa[q]], b.p[pb[q]], v);
           else v = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.q[pa[q]], b.q[pb[q]], v, 0, 0, 0);
         }
-        dA[0][ct] = v;
+        if (kApart) dA[0][ct] += v;
+        else dA[0][ct] = v;
         if (ct + 1 < RT) b = next;
       }
     }
