@@ -205,7 +205,7 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const int row = c.coord(ri) + r, col = 16 * ct + lr;
-          if (row < D && col < D) part[row * D + col] += c.dA[ri][ct][r];
+          if (row < D && col < D) part[row * D + col] += ldexpf(c.dA[ri][ct][r], c.e_all);
           c.dA[ri][ct][r] = 0.f;
         }
   };
@@ -213,13 +213,15 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
   // Points are dealt to the workgroups in a fixed order (every point costs
   // the same K iterations), so each workgroup's partial sums of dA, dM, dQ and
   // deps, and with them the gradients, are the same from call to call.
+  c.scale_of_all(b, blockIdx.x, gridDim.x);
   for (int64_t pt = blockIdx.x; pt < a.n; pt += gridDim.x) {
-    const float w = b.grad_phi[pt];
-    if (w == 0.f || lt_bad_point<D>(a, pt)) {
+    const float w_out = b.grad_phi[pt];
+    if (w_out == 0.f || lt_bad_point<D>(a, pt)) {
       for (int i = tid; i < D; i += S::kThreads) b.dphi_dx[pt * D + i] = 0.f;
       continue;
     }
     c.set_point(a, pt);
+    const float w = c.scale_of_point(w_out);
     const float* ck_pt = a.ckpt + pt * (a.n_ckpt + 1) * slot;
     f4 xb0[RPW], zb0[RPW];  // node 0's adjoints (d <= 32)
     float s1 = 0.f, s2 = 0.f;
@@ -227,7 +229,7 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
     // ---- adjoint of the value at the final iterate: XB, PB; dA += w delta sum p_j x_j^T ----
     {
       const float* last = ck_pt + a.n_ckpt * slot;
-      const float wd = w * c.delta;
+      const float wd = w * c.ds;
       for (int i = tid; i < D; i += S::kThreads) c.sX0[i] = last[i];
       if constexpr (C::kRows) {
         c.load_nodes(last, c.X);
@@ -253,7 +255,7 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
         c.sXb0[i] = c.sE[i] = xb;
         c.sZb0[i] = 0.f;
       }
-      for (int e = tid; e < DD; e += S::kThreads) part[2 * DD + e] += 0.5f * w * c.sX0[e / D] * c.sX0[e % D];
+      for (int e = tid; e < DD; e += S::kThreads) part[2 * DD + e] += 0.5f * w_out * c.sX0[e / D] * c.sX0[e % D];
       if constexpr (C::kRows) {
         float sp = 0.f;
         c.load_matrices(a);
@@ -411,13 +413,13 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
             for (int ct = 0; ct < RT; ct++)
 #pragma unroll
               for (int r = 0; r < 4; r++)
-                if (16 * c.wave + 4 * lk + r < D && 16 * ct + lr < D) pm[r * D + 16 * ct] += acc[ct][r];
+                if (16 * c.wave + 4 * lk + r < D && 16 * ct + lr < D) pm[r * D + 16 * ct] += ldexpf(acc[ct][r], c.e_dM);
           }
         }
         __syncthreads();
       }
     }
-    c.deps += c.lam * s2 - tau * c.delta * s1;
+    c.deps += a.sigma * c.ds * s2 - tau * c.ds * s1;
     // d phi / d x: every x_j^0 = x + noise (j < N), x_N = x, z^0 = x^0
     if constexpr (C::kRows)
 #pragma unroll
@@ -431,7 +433,7 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const float v = group_sum<16>(g[r]);
-          if (lr == 0 && c.rows_ok(ri)) b.dphi_dx[pt * D + c.coord(ri) + r] = v;
+          if (lr == 0 && c.rows_ok(ri)) b.dphi_dx[pt * D + c.coord(ri) + r] = ldexpf(v, c.e_w);
         }
       }
     __syncthreads();
@@ -445,10 +447,10 @@ __device__ __forceinline__ void lt_backward_wave(const LtBwdArgs& b, float* smem
       for (int ct = 0; ct < RT; ct++)
 #pragma unroll
         for (int r = 0; r < 4; r++)
-          part[DD + (c.coord(ri) + r) * D + 16 * ct + lr] = c.dM[ri][ct][r];
+          part[DD + (c.coord(ri) + r) * D + 16 * ct + lr] = ldexpf(c.dM[ri][ct][r], c.e_dM);
   float zero = 0.f;
   c.sum2(c.deps, zero);
-  if (tid == 0) part[3 * DD] = c.deps;
+  if (tid == 0) part[3 * DD] = ldexpf(c.deps, c.e_all);
 }
 
 template <int D, int NT>

@@ -82,7 +82,14 @@ struct LtBack : LtCore<D, NT, KIND, true> {
   Tiles XB, ZB, PB;
   f4 dA[RPW][RT];
   f4 dM[S::kReg ? RPW : 1][S::kReg ? RT : 1];
-  float deps;
+  float deps;  // in units of 2^e_all
+  // The adjoints are linear in the point's output weight w.  bfloat16 pieces lose
+  // their low bits below about 2^-110 (w = 1e-35: dphi/dx 3e-7 -> 5e-6 from 64 bits),
+  // so the sweep runs with w 2^-e_w in [1/2, 1), dA's and deps' terms are taken
+  // relative to 2^e_all, the largest w delta of the workgroup's points, and dM's
+  // relative to 2^e_dM, the largest w.  All are powers of two: the same bits.
+  int e_w, e_all, e_dM;
+  float ds;  // delta 2^(e_w - e_all)
   uint32_t tr0, tr1, tr2;  // transposed-read offsets: nodes 8 lk, 8 lk + 4, 4 lk
 
   __device__ void setup_back(const LtArgs& a, float* lds) {
@@ -93,6 +100,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
     tr1 = at(8 * (lk & 1) + 4 + n) + (lk >> 1) * 16 * 8;
     tr2 = at(4 * lk + n);
     deps = 0.f;
+    e_w = e_all = e_dM = 0;
 #pragma unroll
     for (int ri = 0; ri < RPW; ri++)
 #pragma unroll
@@ -103,6 +111,36 @@ struct LtBack : LtCore<D, NT, KIND, true> {
 #pragma unroll
         for (int ct = 0; ct < RT; ct++) dM[ri][ct] = f4{0.f, 0.f, 0.f, 0.f};
   }
+
+  // e_all and e_dM of the points first, first + step, ... (every wave for itself)
+  __device__ void scale_of_all(const LtBwdArgs& b, int64_t first, int64_t step) {
+    constexpr int kNone = -1024;
+    int e = kNone, em = kNone;
+    for (int64_t pt = first + (tid & 63) * step; pt < b.f.n; pt += 64 * step) {
+      const float w = b.grad_phi[pt], t = b.f.t[pt];
+      const int N = b.f.N[pt];
+      if (w != 0.f && __builtin_isfinite(w) && t > 0.f && __builtin_isfinite(t) && N >= 1 && N <= b.f.N_max) {
+        const int ew = __builtin_amdgcn_frexp_expf(w);
+        em = max(em, ew);
+        e = max(e, ew + __builtin_amdgcn_frexp_expf(t / float(N)));
+      }
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+      e = max(e, __shfl_xor(e, m, 64));
+      em = max(em, __shfl_xor(em, m, 64));
+    }
+    e_all = __builtin_amdgcn_readfirstlane(e == kNone ? 0 : e);
+    e_dM = __builtin_amdgcn_readfirstlane(em == kNone ? 0 : em);
+  }
+  // Takes the point's scales from its weight (after set_point) and returns the weight to sweep with.
+  __device__ float scale_of_point(float w) {
+    e_w = __builtin_amdgcn_readfirstlane(__builtin_isfinite(w) ? __builtin_amdgcn_frexp_expf(w) : 0);
+    ds = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(ldexpf(delta, e_w - e_all))));
+    return ldexpf(w, -e_w);
+  }
+  // An entry of XB_0 as dM takes it.
+  __device__ __forceinline__ float for_dM(float v) const { return ldexpf(v, e_w - e_dM); }
 
   // ---- outer products over the nodes (d > 32) -------------------------------------------
   // One row tile of an image as an operand: coordinate lr, the nodes along k.
@@ -267,7 +305,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
   // Entry i of node 0's adjoints after a step with vbar_1 = vb, and XB_0 of the
   // next step (sE); this step's XB_0 goes to st for dM.
   __device__ __forceinline__ void node0_entry(int i, float vb, float sigma, float theta, float* st) const {
-    st[i] = this->sE[i];
+    st[i] = for_dM(this->sE[i]);
     const float xb = -theta * this->sZb0[i] + this->sWb[i], zb = -sigma * vb;
     this->sXb0[i] = xb;
     this->sZb0[i] = zb;
@@ -283,6 +321,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
   __device__ __forceinline__ void step(const LtArgs& a, float eps, float* st, float* cur, float* prev, Tiles& pk,
                                        float& touched, f4 (&xb0)[RPW], f4 (&zb0)[RPW], float& s1, float& s2) {
     const float sigma = a.sigma, tau = a.tau, theta = a.theta, td = tau * delta;
+    const float td_s = tau * ds, lam_s = sigma * ds;  // for the outer products
     int np = __builtin_amdgcn_readfirstlane(Np);
     asm volatile("" : "+s"(np));
     const int n0 = this->node_now();
@@ -324,7 +363,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++) {
         const f4 v = this->product_reg(fr, e, ri);
-        if (lr == 0) st4(st + this->coord(ri), e[ri]);
+        if (lr == 0) st4(st + this->coord(ri), f4{for_dM(e[ri][0]), for_dM(e[ri][1]), for_dM(e[ri][2]), for_dM(e[ri][3])});
 #pragma unroll
         for (int r = 0; r < 4; r++) wb[ri][r] = lr == 0 ? v[r] : 0.f;
         xb0[ri] = wb[ri] - theta * zb0[ri];
@@ -332,12 +371,12 @@ struct LtBack : LtCore<D, NT, KIND, true> {
 #pragma unroll
       for (int ri = 0; ri < RPW; ri++)
 #pragma unroll
-        for (int t = 0; t < NT; t++) scratch_put(0, ri, t, -td * pk[ri][t]);
+        for (int t = 0; t < NT; t++) scratch_put(0, ri, t, -td_s * pk[ri][t]);
       outer_scratch();
       fr.load(a.packed, 0, 0, lane);
     } else if constexpr (kRows) {
 #pragma unroll
-      for (int t = 0; t < NT; t++) this->put(this->img3, nullptr, t, -td * pk[0][t]);
+      for (int t = 0; t < NT; t++) this->put(this->img3, nullptr, t, -td_s * pk[0][t]);
       fr.load(a.packed, 0, wave, lane);  // arrives during the outer product
       this->fence();
       outer(this->img3, this->imgX);
@@ -382,10 +421,10 @@ struct LtBack : LtCore<D, NT, KIND, true> {
           else PB[ri][t] = vb;
           if constexpr (S::kReg) {
             scratch_put(0, ri, t, vb);
-            scratch_put(1, ri, t, lam * xk);
+            scratch_put(1, ri, t, lam_s * xk);
           } else {
             this->put(this->imgP, this->tailP, t, vb);
-            this->put(this->img3, nullptr, t, lam * xk);
+            this->put(this->img3, nullptr, t, lam_s * xk);
           }
         }
       });

@@ -385,3 +385,28 @@ def test_rounding_of_the_matrix_gradient(oracle_mod, d, N, K):
     err = np.linalg.norm(g["dh"][1:] - want) / np.linalg.norm(want)
     print("d = %d, N = %d: rms error of dphi/dA %.3g" % (d, N, err))
     assert err <= 1.5e-6
+
+
+@pytest.mark.parametrize("power", [-116, 100])
+@pytest.mark.parametrize("d", [16, 32, 100, 128])
+def test_gradients_scale_with_the_output_weights(d, power):
+    """Gradients are linear in grad_phi, and a power of two is exact: very small
+    and very large weights give the same digits, for all points or for some
+    beside others of ordinary weight.  What FP32 cannot hold is below 2^-149,
+    1e-9 of the largest entry here."""
+    w = _small_workload(d=d, n=6, N=20, K=60, seed=80 + d)
+    wts = _f32(np.random.default_rng(d).uniform(0.5, 1.5, w.n))
+    one = _gpu_lt(w, 60, 25, wts)
+    f = 2.0 ** power
+    g = _gpu_lt(w, 60, 25, wts * f)
+    for k in ("dx", "dh", "dg"):
+        assert np.max(np.abs(g[k] / f - one[k])) <= 1e-7 * np.max(np.abs(one[k])), k
+    s = np.where(np.arange(w.n) % 2, f, 1.0)
+    g = _gpu_lt(w, 60, 25, wts * s)
+    for i in range(w.n):
+        assert np.max(np.abs(g["dx"][i] / s[i] - one["dx"][i])) <= 1e-7 * np.max(np.abs(one["dx"][i])), i
+    # the parameters' gradients are those of the points whose weights count
+    big = s == s.max()
+    alone = _gpu_lt(w, 60, 25, wts * big * s)
+    for k in ("dh", "dg"):
+        assert np.max(np.abs(g[k] - alone[k])) <= 1e-7 * np.max(np.abs(alone[k])), k
