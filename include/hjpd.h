@@ -283,7 +283,9 @@ int hjpd_solve_batch_noalloc(hjpd_ctx *ctx, int64_t n, const void *x, const void
  * forward iterate stored every ckpt_every iterations and each segment
  * recomputed during the reverse sweep.  dh_params / dg_params are
  * overwritten (not accumulated).  EINVAL: K_iters < 1, ckpt_every < 1,
- * required pointer NULL; EUNSUPPORTED: other families or float64.
+ * required pointer NULL; EUNSUPPORTED: other families or float64; EDEVICE on a
+ * stream that is being captured (the context's reverse-mode buffers grow on
+ * demand and would leave a captured call their old addresses).
  */
 int hjpd_value_grad(hjpd_ctx *ctx, int64_t n, const void *x, const void *t, const int32_t *N,
                     const void *h_params, const void *g_params, const void *grad_phi, int K_iters,

@@ -860,6 +860,10 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
                   void* dh, void* dg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, int* launches,
                   bool* timing_valid) {
   if (timing_valid) *timing_valid = false;
+  // a captured call would keep the addresses of buffers that a later call may replace
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  LT_HIP(hipStreamIsCapturing(s, &capture), "hipStreamIsCapturing");
+  if (capture != hipStreamCaptureStatusNone) return hjpd_fail(HJPD_EDEVICE, "value_grad on a stream that is being captured");
   if (E > K) E = K;
   const int n_ckpt = (K + E - 1) / E;
   const size_t CK = size_t(d.N_max + 1) * d.d;

@@ -410,3 +410,30 @@ def test_gradients_scale_with_the_output_weights(d, power):
     alone = _gpu_lt(w, 60, 25, wts * big * s)
     for k in ("dh", "dg"):
         assert np.max(np.abs(g[k] - alone[k])) <= 1e-7 * np.max(np.abs(alone[k])), k
+
+
+def test_value_and_gradient_refuse_capture():
+    """The reverse sweep's buffers grow with the largest call and are replaced
+    then, so a captured call, which keeps their addresses, is refused."""
+    import torch
+
+    from paper_1803_01215_amd.autograd import LinearTanhValue
+    w = _small_workload(n=3, K=10)
+    lt = LinearTanhValue(w.d, w.N_max, w.sigma, w.tau, 10, ckpt_every=5, seed=w.init_seed)
+    T = lambda a: torch.tensor(a, dtype=torch.float32, device="cuda")
+    args = (T(w.x), T(w.t), torch.tensor(w.N, device="cuda"), T(w.hp), T(w.gp), torch.ones(3, device="cuda"))
+    want = lt.value_grad(*args)
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph.capture_begin()
+        try:
+            with pytest.raises(Exception, match="captured"):
+                lt.value_grad(*args, stream=stream)
+        finally:
+            graph.capture_end()
+    got = lt.value_grad(*args)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    lt.close()
