@@ -875,8 +875,12 @@ int lt_value_grad(LtState* st, const hjpd_desc& d, int64_t n, const void* x, con
   // several small workgroups share a CU; with long segments their buffers are
   // held to 4 GiB together, down to one workgroup a CU
   const int64_t fit = std::max<int64_t>(st->n_cu, int64_t((size_t(4) << 30) / seg_wg));
-  const int grid_b = int(std::min<int64_t>(lt_grid(st, kb.fn, kb.threads, kb.lds, n), fit));
-  rc = grow((void**)&st->seg, &st->seg_bytes, seg_wg * size_t(grid_b), s);
+  int grid_b = int(std::min<int64_t>(lt_grid(st, kb.fn, kb.threads, kb.lds, n), fit));
+  // where they do not fit the GPU's free memory, fewer workgroups take the points
+  while ((rc = grow((void**)&st->seg, &st->seg_bytes, seg_wg * size_t(grid_b), s)) == HJPD_ENOMEM && grid_b > 1) {
+    (void)hipGetLastError();
+    grid_b = (grid_b + 1) / 2;
+  }
   if (rc) return rc;
   rc = grow((void**)&st->part, &st->part_bytes, sizeof(float) * size_t(grid_b) * (3 * dd + 1), s);
   if (rc) return rc;

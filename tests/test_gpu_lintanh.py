@@ -437,3 +437,29 @@ def test_value_and_gradient_refuse_capture():
     for a, b in zip(got, want):
         assert torch.equal(a, b)
     lt.close()
+
+
+def test_segment_buffers_that_do_not_fit_take_fewer_workgroups():
+    """One segment of 4,000 iterations at d = 100 takes 64 MB per workgroup,
+    16 GB for a workgroup on each of 256 CUs; with 8 GB free the call runs on
+    fewer, and only the order of the sums over points changes."""
+    import torch
+
+    from paper_1803_01215_amd.autograd import LinearTanhValue
+    K, n = 4000, 260
+    w = _small_workload(d=100, n=n, N=4, K=K)
+    T = lambda a: torch.tensor(a, dtype=torch.float32, device="cuda")
+    args = (T(w.x), T(w.t), torch.tensor(w.N, device="cuda"), T(w.hp), T(w.gp), torch.ones(n, device="cuda"))
+    res, held = [], None
+    for E, short in ((100, False), (K, True)):
+        lt = LinearTanhValue(w.d, w.N_max, w.sigma, w.tau, K, ckpt_every=E, seed=w.init_seed)
+        if short:
+            torch.cuda.empty_cache()
+            held = torch.empty(torch.cuda.mem_get_info()[0] - (8 << 30), dtype=torch.uint8, device="cuda")
+        res.append([v.cpu().numpy() for v in lt.value_grad(*args)])
+        torch.cuda.synchronize()
+        lt.close()
+    del held
+    torch.cuda.empty_cache()
+    for a, b in zip(*res):
+        assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(b))
