@@ -943,11 +943,13 @@ __global__ void __launch_bounds__(256, (kShiftWaves<T, K>)) k_group_control_shif
   // node-0 prox as m v + f (first lane; identity elsewhere) when it is affine
   T m0, f0[D];
   const bool aff0 = F::prox0_affine(P, first, m0, f0);
-  // FP64 Hopf tiles of at most 16 lanes with two nodes of d = 10 have no register
-  // left for the inner loop's form: 16x2 on 65,536 points 12.8 ms with the rare
-  // block inside the loop and 14.4 with it outside (32x2: 14.1 and 13.3).  They
-  // keep it inside, and the sines and cosines too.
-  constexpr bool kInner = !(sizeof(T) == 8 && kHopf && L <= 16 && K * D >= 20);
+  // The FP64 Hopf tile 16x2 of d = 10, whose 256 registers at two waves per SIMD spill,
+  // has none for the inner loop's form: 7.5 ms with the rare block inside the
+  // loop, 8.6 with it outside (65,536 points, N = 32, cap 400).  It keeps it inside,
+  // and the sines and cosines too.  Outside is better in the others: 10,007 points,
+  // inside and outside, 8x2 1.18 / 1.12, 8x3 1.97 / 1.75, 16x3 2.78 / 2.62, 8x4 2.84 /
+  // 2.67, 32x2 2.66 / 2.51 ms; 16x4 4.11 / 4.15 (one wave per SIMD).
+  constexpr bool kInner = !(sizeof(T) == 8 && kHopf && L == 16 && K * D == 20);
   // With c(x) = 1 the sines and cosines, most of an FP64 iteration's
   // instructions in few dimensions, are left out: a wave-uniform branch, 3.52 ->
   // 1.33 ms for 256 points of d = 2 and 13.7 -> 4.45 ms for 20,000; d = 10 with
