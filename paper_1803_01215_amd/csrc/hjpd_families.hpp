@@ -33,7 +33,7 @@ struct CNorm {
   static constexpr int D = D_;
   static constexpr int kWavesK[5] = {0, 4, 3, 2, 2};  // FP32 waves per SIMD by nodes per lane
   static constexpr bool kGame = false;
-  static constexpr bool kSplit = false;  // built as split tiles too
+  static constexpr bool kSplit = false;  // no split tiles (k_group_control's kS)
   // dual step maps v = 0 to p = 0 exactly (nodes past N stay at p = 0 without a mask)
   static constexpr bool kZeroSafe = true;
   // Hopf formulation (Algorithm 2) available: closed-form conjugates of both g
@@ -320,7 +320,7 @@ struct Quad {
   // cache of a node take about 65 registers
   static constexpr int kWavesK[5] = {0, 3, 2, 2, 2};
   static constexpr bool kGame = false;
-  static constexpr bool kSplit = true;  // built as split tiles too (FP32)
+  static constexpr bool kSplit = true;  // split tiles in FP32 (k_group_control's kS)
   static constexpr bool kZeroSafe = false;
   static constexpr bool kHopf = false;      // no Hopf step in the plain kernel
   static constexpr bool kHopfGroup = true;  // Hopf formulation in k_group_control
@@ -786,7 +786,7 @@ struct Isaacs {
   static constexpr int kWavesK[5] = {0, 4, 3, 2, 2};  // FP32 waves per SIMD by nodes per lane
   static constexpr int DX = 1, DY = 1;
   static constexpr bool kGame = true;
-  static constexpr bool kSplit = false;  // built as split tiles too
+  static constexpr bool kSplit = false;  // no split tiles (k_group_control's kS)
   static constexpr bool kZeroSafe = false;
   static constexpr bool kHopf = false;
   static constexpr bool kMix = false;

@@ -22,13 +22,15 @@
 //   value, the stores and the refill stand outside.  The kernels are bound by
 //   instruction issue (a wave alone on its SIMD issues about nine tenths of
 //   what the SIMD can), and with the rare block inside the loop every iteration
-//   carried its control flow and the register copies that joined its paths:
-//   about 14 % of the instructions of the isaacs tiles, 5-9 % of the others.
-//   Times with the rare block inside and all residual sums formed in every
-//   iteration, against now: 4.01 -> 3.48 ms (256 points, d = 2, FP64), 532 -> 442
-//   us (2,051 points, d = 3, Hopf), 6.23 -> 5.69 ms (65,536 points, d = 10), 48.5 ->
-//   40.2 ms (4,099 quadrotor points), 252 -> 233 ms (65,536 points of the pursuit
-//   game), 14.2 -> 10.9 ms (Isaacs' game).  Running the body twice per
+//   carried its control flow and the register copies that joined its paths.
+//   Vector and scalar instructions per wave and iteration, with it inside and all
+//   residual sums formed in every iteration, and now (counters, fixed iterations):
+//   Isaacs' game 16x2 257 -> 222, eikonal d = 10 16x2 330 -> 298, pursuit game 32x3
+//   755 -> 717, quadrotor 32x2 728 -> 691.  Times (medians, passes one by one): 424 ->
+//   358 us (2,051 points, d = 3, Hopf), 5.80 -> 5.29 ms (65,536 points, d = 10), 9.5 ->
+//   9.0 ms (10,007 points, d = 10, FP64; 2 to 5 % from run to run), 48.1 -> 39.8 ms
+//   (4,099 quadrotor points), 252 -> 230 ms (65,536 points of the pursuit game), 43.8
+//   -> 41.4 ms (4,096 of them), 14 -> 10.3 ms (Isaacs' game).  Running the body twice per
 //   trip, which would save the copies of the costates that an iteration ends
 //   with, spilled instead.  Exceptions stand at kInner.
 //
@@ -76,10 +78,11 @@ __device__ __forceinline__ bool any_lane(bool v) { return __builtin_amdgcn_ballo
 // forms the sums and sees).  About 15 instructions, most of them scalar, where
 // the sums of four residuals over 32 lanes take 45, in chains of dependent
 // lane exchanges; a wave alone on its SIMD waits for each of those.  Measured
-// with the sums in every iteration and so: pursuit game 254 -> 227 ms (65,536
-// points) and 34.9 -> 26.8 ms (300 points), Isaacs' game 11.7 -> 10.3 ms,
-// quadrotor 43.3 -> 39.6 ms.  The eikonal kernel, which has one residual to sum
-// and short iterations, is 2-8 % faster without and does not use it.
+// with the sums in every iteration and so, all else as it is (medians): pursuit
+// game 255 -> 230 ms (65,536 points), 45.5 -> 41.4 (4,096) and 27.7 -> 27.3 (300),
+// Isaacs' game 11.7 -> 10.3 ms, quadrotor 43.4 -> 39.8 ms (4,099).  The eikonal
+// kernel, which has one residual to sum and short iterations, is 2-8 % faster
+// without and does not use it.
 template <int L, typename T>
 __device__ __forceinline__ bool goes_on(T m, T s, T tol, bool active) {
   constexpr uint64_t kHigh = ~uint64_t(0) / (L == 64 ? ~uint64_t(0) : (uint64_t(1) << (L & 63)) - 1) << (L - 1);
@@ -97,7 +100,7 @@ __device__ __forceinline__ bool goes_on(T m, T s, T tol, bool active) {
 // the same operations per node; the order of the sums matters only where they
 // are formed at all.  A small batch ends with its slowest points, one after
 // another iteration on a wave that has the SIMD to itself, and a wave of one
-// node per lane issues 450 instructions an iteration instead of 750.
+// node per lane issues 430 instructions an iteration instead of 690 (32x2).
 // The pair's residual, in its upper lane: the lower lane's share, then the upper
 // lane's terms d[i]^2 in turn.
 template <typename T, int N>
@@ -226,7 +229,9 @@ __global__ void __launch_bounds__(256, (kFamWaves<T, F, K>)) k_group_control(KAr
   const T wl = a.wl, wr = a.wr;  // kW: H weights at an interval's left / right node
   // The weighted rules and FP64 keep one iteration per trip of the outer loop:
   // with what is constant over an inner loop taken out of it, they round
-  // differently, and this iteration amplifies that.
+  // differently, and this iteration amplifies that.  (Counts, statuses and bits
+  // of every other form are those of the loop without the inner one, FP64 games
+  // among them; the FP32 eikonal Hopf tile 16x4 of d = 10 differs by rounding.)
   constexpr bool kInner = sizeof(T) == 4 && !kW;
 
   T x[K][D], p[K][D], z[K][D], x0[D], z0[D];

@@ -785,7 +785,6 @@ static void fill_args(LtArgs& a, LtState* st, const hjpd_desc& d, int64_t n, con
   a.N = N;
   a.hp = (const float*)hp;
   a.Q = (const float*)gp;
-  a.M = st->M;
   a.Mc = st->M + size_t(d.d) * d.d;
   a.Qs = st->M + 2 * size_t(d.d) * d.d;
   a.packed = st->M + 3 * size_t(d.d) * d.d;

@@ -35,15 +35,16 @@
 // waves, matrix instructions and vector ones nearly one after the other
 // (7,900 cycles of the former and 1,700 instructions of the latter a row wave,
 // 36,400 cycles a step and point at d = 100, N = 50; LDS 12,500).  So products
-// run on bfloat16 pieces (six matrix instructions where FP32 ones need sixteen
+// run on bfloat16 pieces (six matrix instructions where FP32 ones need eight
 // of twice the length), nothing is read back for elementwise work, and a wave
 // holds one matrix at a time.  d <= 32: products straight from the state
 // registers on FP32 matrix instructions, outer products by way of LDS rows of
 // one wave, no barrier.  Before, products on FP32 matrix instructions from
 // staged rows with the state in LDS: 2,048 points x 500 iterations at d = 100
-// took 128.4 ms, now 65 ms; d = 128 (512 points, N = 40, 100 iterations) 7.72,
-// now 4.33 ms; d = 32 (777 points, 200 iterations) 4.1, now 0.76 ms.  The error of dphi/dh
-// against 64 bits at the first went from 8.1e-6 to 2.4e-6.
+// took 128 ms, now 68 ms; d = 128 (512 points, N = 40, 100 iterations) 7.7, now
+// 4.4 ms; d = 32 (777 points, N = 24, 200 iterations) 8.4, now 1.4 ms.  Errors from
+// 64 bits (rms) at the first, before and now: dphi/dx 2.2e-6, 1.5e-6; deps and dA
+// together 8.3e-6, 0.8e-7; dQ 2.4e-7, 0.8e-7.
 #pragma once
 
 #include "hjpd_lt_core.hpp"

@@ -141,8 +141,7 @@ struct LtArgs {
   const int32_t* N;
   const float* hp;  // [eps, A (d*d)]
   const float* Q;   // [d*d]
-  const float* M;   // (I + tau Q_s)^{-1}
-  const float* Mc;  // the same as [column / 4][row][4]
+  const float* Mc;  // (I + tau Q_s)^{-1} as [column / 4][row][4]
   const float* Qs;  // (Q + Q^T) / 2
   const float* packed;  // A, A^T (and M, d <= 32) as operands, LtFrag
   float* phi;
@@ -196,7 +195,7 @@ struct LtShape {
   static constexpr int kTh = kThLds && !BACK ? 256 * RT * NT : 0;
   static constexpr bool kPbLds = BACK && !kReg && D < 128;
   static constexpr int kPb = kPbLds ? 256 * RT * NT : 0;
-  // d <= 32: rows of two operands of an outer product, row length 16 mod 64 (conflict-free columns)
+  // d <= 32: rows of two operands of an outer product, row length an odd multiple of 16 (conflict-free columns)
   static constexpr int LDW = D == 16 ? 16 : 48;
   static constexpr int kScratch = BACK && kReg ? 2 * ROWS * LDW : 0;
   static constexpr int kLdsFloats = kImgs * kImg + 2 * kTailF + kM + kVecs * kVec + kTh + kPb + kScratch + 2 * W + 2;
