@@ -344,8 +344,8 @@ def _reference_gradients(O, w, K, wts):
     for i in range(n):
         for j in range(w.N_max + 1):
             for c in range(d):
-                noise[0][i, j, c] = O.init_noise(w.init_seed, i, 0, j, c)
-                noise[1][i, j, c] = O.init_noise(w.init_seed, i, 1, j, c)
+                noise[0][i, j, c] = O.init_noise(w.init_seed, int(w.ids[i]), 0, j, c)
+                noise[1][i, j, c] = O.init_noise(w.init_seed, int(w.ids[i]), 1, j, c)
     T = lambda a: torch.tensor(a, dtype=torch.float64)
     x, A, Q = T(_f32(w.x)).requires_grad_(), T(_f32(w.hp[1:])).reshape(d, d).requires_grad_(), \
         T(_f32(w.gp)).reshape(d, d).requires_grad_()
@@ -463,3 +463,29 @@ def test_segment_buffers_that_do_not_fit_take_fewer_workgroups():
     torch.cuda.empty_cache()
     for a, b in zip(*res):
         assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(b))
+
+
+@pytest.mark.parametrize("d,n", [(16, 9001), (32, 9001), (100, 601), (128, 601)])
+def test_workgroups_that_take_several_points(oracle_mod, d, n):
+    """More points than the persistent grids hold (a workgroup takes its second
+    and third), segments longer than the 32 steps that dM's staging holds.
+    Sampled points against the oracle and binary64 autograd, FP32 bar 1e-4; the
+    parameters' gradients with every other weight zero."""
+    K = 40
+    w = _small_workload(d=d, n=n, N=9, K=K, seed=20 + d)
+    w.N = np.random.default_rng(d).integers(1, 10, n).astype(np.int32)
+    idx = np.array([0, 1, n // 3, n // 2, n - 2, n - 1])
+    ws = w.subset(idx)
+    wts = np.random.default_rng(d + 1).uniform(0.5, 1.5, n)
+    phi, dx, de, dA, dQ = _reference_gradients(oracle_mod, ws, K, wts[idx])
+    g = _gpu_lt(w, K, 50, wts)
+    assert np.all(g["iters"] == K) and np.all(np.isfinite(g["phi"])) and np.all(np.isfinite(g["dx"]))
+    assert rel_err(g["phi"][idx], phi).max() <= 1e-4 and rel_err(g["phi_solve"][idx], phi).max() <= 1e-4
+    assert np.max(np.abs(g["dx"][idx] - dx)) <= 1e-4 * max(1.0, np.abs(dx).max())
+    some = np.zeros(n)
+    some[idx] = wts[idx]
+    g = _gpu_lt(w, K, 50, some)
+    rest = np.setdiff1d(np.arange(n), idx)
+    assert np.all(g["dx"][rest] == 0.0)
+    for got, want in ((g["dx"][idx], dx), (g["dh"][:1], de.reshape(1)), (g["dh"][1:], dA.ravel()), (g["dg"], dQ.ravel())):
+        assert np.max(np.abs(got - want)) <= 1e-4 * max(1.0, np.abs(want).max())
