@@ -179,7 +179,7 @@ struct LtBack : LtCore<D, NT, KIND, true> {
   // with more there are no registers for that (42 % slower at N = 50), and dA is
   // added to the partial sums in memory and cleared every kFlush steps.
   // rms error of dA at d = 100 with FP32 products, straight, and so: 9.0e-7, 2.4e-6,
-  // 1.8e-7 (1,442 points, N 19 to 25, 90 iterations); 1.4e-6, 4.6e-6, 5e-7 (700
+  // 1.8e-7 (1,442 points, N 19 to 25, 90 iterations); 1.4e-6, 4.6e-6, 5.9e-7 (700
   // points, N = 50, 100 iterations).
   static constexpr bool kApart = NT <= 2;
   static constexpr int kFlush = S::kReg || kApart ? 1 << 30 : 16;
